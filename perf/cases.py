@@ -265,7 +265,8 @@ def run(s):
     if kind == "ingest":
         model, prec = _model(case)
         E, nu = _material(case)
-        m = ebbx.FemMesh(s["X"], s["tets"], s["pinned"], model=model, elem_prec=prec, E=E, nu=nu, rho=RHO,
+        # the reordering permutes the bound pinned flags in place, so the pass binds a copy
+        m = ebbx.FemMesh(s["X"], s["tets"], s["pinned"].clone(), model=model, elem_prec=prec, E=E, nu=nu, rho=RHO,
                          strategy=ebbx.STRAT_BLOCK, morton=True)
         at = m.vperm.long()
         f = m.fem.forces(s["d"].index_select(1, at))
