@@ -1563,17 +1563,6 @@ void build_halo(ebbx_fem_s *F, const std::vector<int32_t> &verts, const std::vec
 // vertices at [b*maxv, (b+1)*maxv) padded with -1 (halo positions hpos alike) and
 // its block-relative row starts at [b*(maxv+1), (b+1)*(maxv+1)); per tet the corner
 // rows and the packed slots.
-// Block-local FP32 rest positions: entry (b, i) holds X of block b's i-th vertex minus X of its
-// first vertex, rounded to FP32 (three columns of nblk * S entries; padding 0).
-__global__ void k_block_xf(const double *X, int64_t nv, const int32_t *bverts, int64_t n, uint32_t S, float *xf) {
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t v = bverts[e], v0 = bverts[(e / S) * S];
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            xf[(int64_t)k * n + e] = v >= 0 ? (float)(X[(int64_t)k * nv + v] - X[(int64_t)k * nv + v0]) : 0.0f;
-    }
-}
-
 void upload_block_tables(ebbx_fem_s *F, const HostBlocks &hb, const std::vector<int32_t> &hpos, hipStream_t s) {
     const int64_t nblk = hb.nblk;
     const size_t S = (size_t)hb.maxv;
@@ -1593,7 +1582,6 @@ void upload_block_tables(ebbx_fem_s *F, const HostBlocks &hb, const std::vector<
             }
         }
     }
-    upload(F->blk_vptr, hb.vptr.data(), hb.vptr.size() * sizeof(int32_t), s);
     upload(F->blk_verts, pverts.data(), pverts.size() * sizeof(int32_t), s);
     upload(F->blk_lptr, prow.data(), prow.size() * sizeof(uint16_t), s);
     upload(F->blk_pos, hb.pos.data(), hb.pos.size() * sizeof(uint32_t), s);
@@ -1603,17 +1591,7 @@ void upload_block_tables(ebbx_fem_s *F, const HostBlocks &hb, const std::vector<
     F->nblk = nblk;
     F->blk_maxv = hb.maxv;
     F->blk_w = hb.w;
-    F->blk_nverts = (int64_t)hb.verts.size();
-    // FP32 elements on blocks of at most 256 vertices read block-local FP32 rest positions
-    if (F->prec == EBBX_F32 && hb.w == 1 && nblk > 0) {
-        const int64_t n = nblk * (int64_t)S;
-        F->blk_xf.reset((size_t)n * 3 * sizeof(float), s);
-        hipLaunchKernelGGL(k_block_xf, dim3(grid_n(n, 256, 16384)), dim3(256), 0, s, F->Xc.as<double>(), F->nv,
-                           F->blk_verts.as<int32_t>(), n, (uint32_t)S, F->blk_xf.as<float>());
-        HIPCHK(hipGetLastError());
-    } else {
-        F->blk_xf.release();
-    }
+    build_block_xf(F, s);
 }
 
 void download_keys(const ebbx_fem_s *F, std::vector<int32_t> &keys, std::vector<int64_t> &rp) {
@@ -1621,21 +1599,6 @@ void download_keys(const ebbx_fem_s *F, std::vector<int32_t> &keys, std::vector<
     if (F->nt > 0) HIPCHK(hipMemcpy(keys.data(), F->keys, keys.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
     rp.resize((size_t)(F->nv + 1));
     HIPCHK(hipMemcpy(rp.data(), F->group->row_ptr.get(), rp.size() * sizeof(int64_t), hipMemcpyDeviceToHost));
-}
-
-// The BLOCK tables with a halo of the blocks' shared vertices.
-void build_blocks(ebbx_fem_s *F, int32_t bt, hipStream_t s) {
-    if (bt < 64 || bt > 1024 || bt % 64)
-        fail(EBBX_E_ARG, "block strategy: tets per block must be a multiple of 64 from 64 to 1024 (got %d)", bt);
-    std::vector<int32_t> keys;
-    std::vector<int64_t> rp;
-    download_keys(F, keys, rp);
-    const HostBlocks hb = host_blocks(keys, rp, F->nt, bt);
-    std::vector<int32_t> hpos;
-    build_halo(F, hb.verts, hb.own, rp, hpos, s);
-    upload_block_tables(F, hb, hpos, s);
-    F->halo_level = 0;
-    F->blocks_built = true;
 }
 
 // OWNER tables.  Block b owns vertices [b*vb, min(nv, (b+1)*vb)).  Its tets are

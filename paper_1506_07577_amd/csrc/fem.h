@@ -151,7 +151,7 @@ void elem_energy(ebbx_fem_s *F, const double *d, double *out_dev, hipStream_t s)
 int64_t elem_precompute(ebbx_fem_s *F, const double *X, const double *E_tet, hipStream_t s);
 // Fill n doubles with a value (graph-safe, no memset node).
 void fill_f64(double *p, int64_t n, double v, hipStream_t s);
-// Host form of the tet-block tables (blocks of bt consecutive tets): per block its
+// Host form of the tet-block tables (the PIPE strategy's blocks of bt consecutive tets): per block its
 // sorted vertex list (CSR vptr/verts), each list entry's run of incidence rows
 // (global running starts lptr), whether the block holds every incident tet of the
 // entry's vertex (own), and per tet its corners' rows (pos, two 16-bit pairs) and
@@ -171,8 +171,12 @@ void upload(DevBuf &dst, const void *src, size_t bytes, hipStream_t s);
 void build_halo(ebbx_fem_s *F, const std::vector<int32_t> &verts, const std::vector<uint8_t> &own,
                 const std::vector<int64_t> &rp, std::vector<int32_t> &hpos, hipStream_t s);
 void upload_block_tables(ebbx_fem_s *F, const HostBlocks &hb, const std::vector<int32_t> &hpos, hipStream_t s);
-// Build the tet-block tables of the BLOCK strategy.
+// Build the tet-block tables of the BLOCK strategies with a halo of the blocks' shared vertices,
+// on the device (tables.hip).
 void build_blocks(ebbx_fem_s *F, int32_t tets_per_block, hipStream_t s);
+// The block-local FP32 rest positions of the current block tables (FP32 elements on blocks of at
+// most 256 vertices; released otherwise).
+void build_block_xf(ebbx_fem_s *F, hipStream_t s);
 // Build the super-block tables of the PIPE strategy (blocks of 256 tets, g blocks per
 // super-block) and its halo.
 void build_pipe(ebbx_fem_s *F, int32_t g, hipStream_t s);
@@ -239,11 +243,10 @@ struct ebbx_fem_s {
     int32_t blk_maxv = 0;      // largest vertex count of one block
     int32_t blk_w = 1;         // 32-bit words of packed corner slots per tet
     int32_t blk_red = 0;       // 0: incidence-list sums (deterministic), 1: FP64 LDS atomics
-    int64_t blk_nverts = 0;    // entries of blk_verts over all blocks
     int64_t sh_n = 0;          // vertices summed from the halo (shared or untouched)
     int64_t halo_n = 0;        // halo entries
     ebbx::DevBuf blk_xf;   // block-local FP32 rest positions (FP32 elements, blocks of <= 256 vertices)
-    ebbx::DevBuf blk_vptr, blk_verts, blk_lptr, blk_pos, blk_hpos, blk_local, halo, sh_vert, sh_ptr, sh_pos, sh_tab,
+    ebbx::DevBuf blk_verts, blk_lptr, blk_pos, blk_hpos, blk_local, halo, sh_vert, sh_ptr, sh_pos, sh_tab,
         sh_row;
     ebbx::DevBuf halo9;        // the fused step preamble's halo (9 values per entry)
     int32_t sh_nc = 0;         // int4 chunks per row of sh_tab (0: use the CSR form)

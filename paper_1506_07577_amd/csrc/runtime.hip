@@ -177,17 +177,32 @@ __global__ void k_scan_add(int64_t *data, int64_t n, const int64_t *offs) {
     }
 }
 
-void exclusive_scan_i64(int64_t *data, int64_t n, hipStream_t s) {
-    if (n <= 0) return;
-    int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
-    DevBuf sums((size_t)nb * sizeof(int64_t), s);
-    hipLaunchKernelGGL(k_scan_tile, dim3((unsigned)nb), dim3(SCAN_T), 0, s, data, n, sums.as<int64_t>());
+// Tile totals over all levels of a scan of n entries.
+static int64_t scan_scratch(int64_t n) {
+    int64_t total = 0;
+    do {
+        n = (n + SCAN_TILE - 1) / SCAN_TILE;
+        total += n;
+    } while (n > 1);
+    return total;
+}
+
+// The scan's launches; sums: scan_scratch(n) entries.
+static void scan_levels(int64_t *data, int64_t n, int64_t *sums, hipStream_t s) {
+    const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
+    hipLaunchKernelGGL(k_scan_tile, dim3((unsigned)nb), dim3(SCAN_T), 0, s, data, n, sums);
     HIPCHK(hipGetLastError());
     if (nb > 1) {
-        exclusive_scan_i64(sums.as<int64_t>(), nb, s);
-        hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(SCAN_T), 0, s, data, n, sums.as<int64_t>());
+        scan_levels(sums, nb, sums + nb, s);
+        hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(SCAN_T), 0, s, data, n, sums);
         HIPCHK(hipGetLastError());
     }
+}
+
+void exclusive_scan_i64(int64_t *data, int64_t n, hipStream_t s) {
+    if (n <= 0) return;
+    DevBuf sums((size_t)scan_scratch(n) * sizeof(int64_t), s);
+    scan_levels(data, n, sums.as<int64_t>(), s);
     // keep `sums` alive until the kernels that read it have run
     HIPCHK(hipStreamSynchronize(s));
 }
@@ -267,6 +282,7 @@ static void radix_sort_pairs(K *keys, uint32_t *vals, int64_t n, int bits, hipSt
     const int64_t ntiles = (n + RS_TILE - 1) / RS_TILE;
     DevBuf kb((size_t)n * sizeof(K), s), vb((size_t)n * sizeof(uint32_t), s);
     DevBuf hist((size_t)(256 * ntiles) * sizeof(int64_t), s);
+    DevBuf sums((size_t)scan_scratch(256 * ntiles) * sizeof(int64_t), s);
     K *ka = keys, *kx = kb.as<K>();
     uint32_t *va = vals, *vx = vb.as<uint32_t>();
     int passes = (bits + 7) / 8;
@@ -275,7 +291,7 @@ static void radix_sort_pairs(K *keys, uint32_t *vals, int64_t n, int bits, hipSt
         hipLaunchKernelGGL(k_rs_hist<K>, dim3((unsigned)ntiles), dim3(RS_T), 0, s, ka, n, shift, ntiles,
                            hist.as<int64_t>());
         HIPCHK(hipGetLastError());
-        exclusive_scan_i64(hist.as<int64_t>(), 256 * ntiles, s);
+        scan_levels(hist.as<int64_t>(), 256 * ntiles, sums.as<int64_t>(), s);
         hipLaunchKernelGGL(k_rs_scatter<K>, dim3((unsigned)ntiles), dim3(RS_T), 0, s, ka, va, kx, vx, n,
                            shift, ntiles, hist.as<int64_t>());
         HIPCHK(hipGetLastError());

@@ -1,0 +1,336 @@
+// tables.hip -- the tables of the BLOCK strategies, built on the device.
+//
+// Blocks of bt consecutive tets.  Per block: the sorted set of vertices it touches,
+// each corner's slot in that set, the block's incidences ordered by (vertex, local
+// tet, corner) with each corner's row in that order and each vertex's run of rows,
+// and whether the block holds every incident tet of the vertex.  Vertices that it
+// does not own outright get a place in the halo; the shared-vertex tables list each
+// such vertex's halo places in block order.
+//
+// One workgroup sorts a block's 4 bt (vertex, incidence) pairs in LDS, once to count
+// (vertices per block fix the tables' stride, shared vertices the halo's places) and
+// once to write: sorting 8 KiB in LDS twice costs less than keeping the sorted pairs
+// of every block in memory between the passes.  Bound by the barriers of the sort's
+// stages.  The tables equal those of host_blocks (elem.hip) entry for entry.
+// Measured, a new scrambled mesh of 358k tets taken in (relations, Morton order, domain,
+// mass, one force; FP32): 71.9 ms with the tables built on the host and each pass of the
+// radix sort waited for, 1.60 ms with these.
+#include <algorithm>
+
+#include "fem.h"
+
+namespace ebbx {
+
+namespace {
+
+constexpr int BT_THREADS = 256;
+
+// ---- a block's pairs, sorted ---------------------------------------------------------------
+
+// Load the pairs (vertex << 12 | 4 * local tet + corner) of block b into s[0, n), n a power of
+// two >= 4 bt, absent ones as the largest value, and sort them (bitonic, ascending).
+__device__ __forceinline__ void sorted_pairs(const int32_t *keys, int64_t nt, int64_t b, int32_t bt, int32_t n,
+                                             unsigned long long *s) {
+    const int tid = threadIdx.x;
+    const int64_t t0 = b * bt;
+    for (int32_t e = tid; e < n; e += BT_THREADS) {
+        const int32_t c = e / bt, tl = e - c * bt;   // coalesced along each key column
+        const bool in = c < 4 && t0 + tl < nt;
+        const int32_t i = c < 4 ? 4 * tl + c : e;
+        s[i] = in ? ((unsigned long long)(uint32_t)keys[(int64_t)c * nt + t0 + tl] << 12) | (unsigned)i : ~0ull;
+    }
+    __syncthreads();
+    for (int32_t k = 2; k <= n; k <<= 1)
+        for (int32_t j = k >> 1; j > 0; j >>= 1) {
+            for (int32_t e = tid; e < n / 2; e += BT_THREADS) {
+                const int32_t i = ((e & ~(j - 1)) << 1) | (e & (j - 1)), o = i | j;
+                const unsigned long long x = s[i], y = s[o];
+                if ((x > y) == ((i & k) == 0)) {
+                    s[i] = y;
+                    s[o] = x;
+                }
+            }
+            __syncthreads();
+        }
+}
+
+// Exclusive prefix of x over the workgroup's threads and the total (sw: one entry per wave).
+__device__ __forceinline__ int32_t block_prefix(int32_t x, int32_t *sw, int32_t &total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t v = x;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t y = __shfl_up(v, o, 64);
+        if (lane >= o) v += y;
+    }
+    __syncthreads();
+    if (lane == 63) sw[wave] = v;
+    __syncthreads();
+    int32_t off = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < BT_THREADS / 64; ++w) {
+        if (w < wave) off += sw[w];
+        total += sw[w];
+    }
+    return off + v - x;
+}
+
+// Thread tid's stretch of the sorted pairs, [tid * n / 256, ...): head h of a vertex's run, with
+// the run's length, is passed to f(i, vertex, length, shared).
+template <class F>
+__device__ __forceinline__ void each_head(const unsigned long long *s, int32_t n, const int64_t *rp, F f) {
+    const int32_t per = n / BT_THREADS, i0 = (int32_t)threadIdx.x * per;
+    for (int32_t i = i0; i < i0 + per; ++i) {
+        if (s[i] == ~0ull) break;
+        const uint32_t v = (uint32_t)(s[i] >> 12);
+        if (i > 0 && (uint32_t)(s[i - 1] >> 12) == v) continue;
+        int32_t j = i + 1;
+        while (j < n && s[j] != ~0ull && (uint32_t)(s[j] >> 12) == v) ++j;
+        f(i, v, j - i, (int64_t)(j - i) != rp[v + 1] - rp[v]);
+    }
+}
+
+// Pass 1: the block's shared vertices into nsh[b], the largest vertex count of a block into *maxv.
+__global__ __launch_bounds__(BT_THREADS) void k_blk_count(const int32_t *keys, const int64_t *rp, int64_t nt,
+                                                          int32_t bt, int32_t n, int64_t *nsh, int *maxv) {
+    extern __shared__ unsigned long long s_pairs[];
+    __shared__ int32_t sw[BT_THREADS / 64];
+    const int64_t b = blockIdx.x;
+    sorted_pairs(keys, nt, b, bt, n, s_pairs);
+    int32_t heads = 0, shared = 0;
+    each_head(s_pairs, n, rp, [&](int32_t, uint32_t, int32_t, bool sh) {
+        ++heads;
+        shared += sh;
+    });
+    int32_t nb = 0, ns = 0;
+    block_prefix(heads, sw, nb);
+    block_prefix(shared, sw, ns);
+    if (threadIdx.x == 0) {
+        nsh[b] = ns;
+        atomicMax(maxv, nb);
+    }
+}
+
+struct BlkOut {
+    int32_t *verts, *hpos;      // [nblk * S], -1 padded
+    uint16_t *row;              // [nblk * (S + 1)]
+    uint32_t *pos, *slot;       // [2 nt], [w nt]
+    uint32_t *hkey, *hval;      // per halo place: its vertex, the place
+    int32_t *cnt;               // per vertex: its halo places
+};
+
+// Pass 2: the tables of block b; its halo places start at hbase[b].
+__global__ __launch_bounds__(BT_THREADS) void k_blk_fill(const int32_t *keys, const int64_t *rp, int64_t nt,
+                                                         int32_t bt, int32_t n, int32_t S, int32_t w,
+                                                         const int64_t *hbase, BlkOut o) {
+    extern __shared__ unsigned long long s_pairs[];
+    uint32_t *s_at = (uint32_t *)(s_pairs + n);   // per incidence: slot << 16 | row
+    __shared__ int32_t sw[BT_THREADS / 64];
+    const int64_t b = blockIdx.x;
+    const int tid = threadIdx.x;
+    sorted_pairs(keys, nt, b, bt, n, s_pairs);
+    int32_t heads = 0, shared = 0;
+    each_head(s_pairs, n, rp, [&](int32_t, uint32_t, int32_t, bool sh) {
+        ++heads;
+        shared += sh;
+    });
+    int32_t nb = 0, ns = 0;
+    int32_t slot = block_prefix(heads, sw, nb);
+    int64_t hp = hbase[b] + block_prefix(shared, sw, ns);
+    const int64_t left = nt - b * bt;
+    const int32_t ntl = left < bt ? (int32_t)left : bt;   // tets of this block
+    each_head(s_pairs, n, rp, [&](int32_t i, uint32_t v, int32_t len, bool sh) {
+        const int64_t q = b * S + slot;
+        o.verts[q] = (int32_t)v;
+        o.row[b * (S + 1) + slot] = (uint16_t)i;
+        o.hpos[q] = sh ? (int32_t)hp : -1;
+        if (sh) {
+            o.hkey[hp] = v;
+            o.hval[hp] = (uint32_t)hp;
+            atomicAdd(o.cnt + v, 1);
+            ++hp;
+        }
+        for (int32_t j = i; j < i + len; ++j) s_at[s_pairs[j] & 4095u] = ((uint32_t)slot << 16) | (uint32_t)j;
+        ++slot;
+    });
+    for (int32_t i = nb + tid; i <= S; i += BT_THREADS) {
+        o.row[b * (S + 1) + i] = (uint16_t)(4 * ntl);
+        if (i < S) {
+            o.verts[b * S + i] = -1;
+            o.hpos[b * S + i] = -1;
+        }
+    }
+    __syncthreads();
+    for (int32_t tl = tid; tl < ntl; tl += BT_THREADS) {
+        const int64_t t = b * bt + tl;
+        const uint32_t a0 = s_at[4 * tl], a1 = s_at[4 * tl + 1], a2 = s_at[4 * tl + 2], a3 = s_at[4 * tl + 3];
+        o.pos[t] = (a0 & 0xffffu) | (a1 << 16);
+        o.pos[nt + t] = (a2 & 0xffffu) | (a3 << 16);
+        if (w == 1) {   // 4 x 8 bits: every block has at most 256 vertices
+            o.slot[t] = (a0 >> 16) | ((a1 >> 16) << 8) | ((a2 >> 16) << 16) | ((a3 >> 16) << 24);
+        } else {
+            o.slot[t] = (a0 >> 16) | (a1 & 0xffff0000u);
+            o.slot[nt + t] = (a2 >> 16) | (a3 & 0xffff0000u);
+        }
+    }
+}
+
+// ---- shared vertices -------------------------------------------------------------------------
+
+// A vertex has a row in the shared-vertex table if it has halo places, or no tet at all (the halo
+// pass zeroes it).  Scan inputs, and the largest number of places of one vertex into *maxm.
+__global__ void k_sh_flags(const int32_t *cnt, const int64_t *rp, int64_t nv, int64_t *flag, int64_t *places,
+                           int *maxm) {
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v > nv) return;
+    const int32_t c = v < nv ? cnt[v] : 0;
+    flag[v] = v < nv && (c > 0 || rp[v + 1] == rp[v]);
+    places[v] = c;
+    if (c > 0) atomicMax(maxm, c);
+}
+
+__global__ void k_sh_rows(const int32_t *cnt, const int64_t *rp, int64_t nv, const int64_t *row, const int64_t *ptr,
+                          int32_t *sh_vert, int32_t *sh_ptr, int32_t *sh_row) {
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v > nv) return;
+    if (v == nv) {
+        sh_ptr[row[nv]] = (int32_t)ptr[nv];
+        return;
+    }
+    const bool on = cnt[v] > 0 || rp[v + 1] == rp[v];
+    sh_row[v] = on ? (int32_t)row[v] : -1;
+    if (on) {
+        sh_vert[row[v]] = (int32_t)v;
+        sh_ptr[row[v]] = (int32_t)ptr[v];
+    }
+}
+
+// Fixed-width rows of w halo places, -1 padded.
+__global__ void k_sh_tab(const int32_t *sh_ptr, const int32_t *sh_pos, int64_t sh_n, int32_t w, int32_t *tab) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= sh_n * w) return;
+    const int64_t r = i / w;
+    const int32_t j = sh_ptr[r] + (int32_t)(i - r * w);
+    tab[i] = j < sh_ptr[r + 1] ? sh_pos[j] : -1;
+}
+
+// Block-local FP32 rest positions: entry (b, i) holds X of block b's i-th vertex minus X of its
+// first vertex, rounded to FP32 (three columns of nblk * S entries; padding 0).
+__global__ void k_block_xf(const double *X, int64_t nv, const int32_t *bverts, int64_t n, uint32_t S, float *xf) {
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t v = bverts[e], v0 = bverts[(e / S) * S];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            xf[(int64_t)k * n + e] = v >= 0 ? (float)(X[(int64_t)k * nv + v] - X[(int64_t)k * nv + v0]) : 0.0f;
+    }
+}
+
+unsigned grid_of(int64_t n, int per) { return (unsigned)std::max<int64_t>(1, (n + per - 1) / per); }
+
+}  // namespace
+
+void build_block_xf(ebbx_fem_s *F, hipStream_t s) {
+    const int64_t n = F->nblk * (int64_t)F->blk_maxv;
+    if (F->prec != EBBX_F32 || F->blk_w != 1 || F->nblk == 0) {
+        F->blk_xf.release();
+        return;
+    }
+    F->blk_xf.reset((size_t)n * 3 * sizeof(float), s);
+    hipLaunchKernelGGL(k_block_xf, dim3(std::min<unsigned>(grid_of(n, 256), 16384)), dim3(256), 0, s,
+                       F->Xc.as<double>(), F->nv, F->blk_verts.as<int32_t>(), n, (uint32_t)F->blk_maxv,
+                       F->blk_xf.as<float>());
+    HIPCHK(hipGetLastError());
+}
+
+void build_blocks(ebbx_fem_s *F, int32_t bt, hipStream_t s) {
+    if (bt < 64 || bt > 1024 || bt % 64)
+        fail(EBBX_E_ARG, "block strategy: tets per block must be a multiple of 64 from 64 to 1024 (got %d)", bt);
+    const int64_t nt = F->nt, nv = F->nv, nblk = (nt + bt - 1) / bt;
+    const int64_t *rp = F->group->row_ptr.as<int64_t>();
+    int32_t n = 256;
+    while (n < 4 * bt) n <<= 1;
+    F->blocks_built = false;   // until the tables below are whole
+    F->halo_level = -1;
+    // pass 1
+    DevBuf nsh((size_t)(nblk + 1) * sizeof(int64_t), s), mx(2 * sizeof(int), s);
+    HIPCHK(hipMemsetAsync(mx.get(), 0, 2 * sizeof(int), s));
+    HIPCHK(hipMemsetAsync(nsh.get(), 0, (size_t)(nblk + 1) * sizeof(int64_t), s));
+    if (nblk > 0) {
+        hipLaunchKernelGGL(k_blk_count, dim3((unsigned)nblk), dim3(BT_THREADS), (size_t)n * 8, s, F->keys, rp, nt, bt,
+                           n, nsh.as<int64_t>(), mx.as<int>());
+        HIPCHK(hipGetLastError());
+    }
+    exclusive_scan_i64(nsh.as<int64_t>(), nblk + 1, s);
+    int maxv = 0;
+    int64_t nh = 0;
+    HIPCHK(hipMemcpyAsync(&maxv, mx.get(), sizeof maxv, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(&nh, nsh.as<int64_t>() + nblk, sizeof nh, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    if (nh >= (int64_t(1) << 31)) fail(EBBX_E_ARG, "block tables exceed int32");
+    const int32_t S = std::max(maxv, 1), w = maxv <= 256 ? 1 : 2;
+    // pass 2
+    auto room = [](int64_t count, size_t each) { return std::max<size_t>((size_t)count * each, 16); };
+    F->blk_verts.reset(room(nblk * S, 4), s);
+    F->blk_hpos.reset(room(nblk * S, 4), s);
+    F->blk_lptr.reset(room(nblk * (S + 1), 2), s);
+    F->blk_pos.reset(room(2 * nt, 4), s);
+    F->blk_local.reset(room(w * nt, 4), s);
+    F->sh_pos.reset(room(nh, 4), s);
+    DevBuf hkey(room(nh, 4), s), cnt(room(nv, 4), s);
+    HIPCHK(hipMemsetAsync(cnt.get(), 0, cnt.bytes(), s));
+    if (nblk > 0) {
+        const BlkOut o{F->blk_verts.as<int32_t>(), F->blk_hpos.as<int32_t>(), F->blk_lptr.as<uint16_t>(),
+                       F->blk_pos.as<uint32_t>(), F->blk_local.as<uint32_t>(), hkey.as<uint32_t>(),
+                       F->sh_pos.as<uint32_t>(), cnt.as<int32_t>()};
+        hipLaunchKernelGGL(k_blk_fill, dim3((unsigned)nblk), dim3(BT_THREADS), (size_t)n * 12, s, F->keys, rp, nt, bt,
+                           n, S, w, nsh.as<int64_t>(), o);
+        HIPCHK(hipGetLastError());
+    }
+    F->blk_tets = bt;
+    F->nblk = nblk;
+    F->blk_maxv = S;
+    F->blk_w = w;
+    F->halo_n = nh;
+    build_block_xf(F, s);
+    // each shared vertex's places, ascending: a stable sort of the places by vertex
+    int bits = 1;
+    while ((int64_t(1) << bits) < nv) ++bits;
+    radix_sort_pairs_u32(hkey.as<uint32_t>(), F->sh_pos.as<uint32_t>(), nh, bits, s);
+    DevBuf row((size_t)(nv + 1) * sizeof(int64_t), s), ptr((size_t)(nv + 1) * sizeof(int64_t), s);
+    hipLaunchKernelGGL(k_sh_flags, dim3(grid_of(nv + 1, 256)), dim3(256), 0, s, cnt.as<int32_t>(), rp, nv,
+                       row.as<int64_t>(), ptr.as<int64_t>(), mx.as<int>() + 1);
+    HIPCHK(hipGetLastError());
+    exclusive_scan_i64(row.as<int64_t>(), nv + 1, s);
+    exclusive_scan_i64(ptr.as<int64_t>(), nv + 1, s);
+    int maxm = 0;
+    int64_t sh_n = 0;
+    HIPCHK(hipMemcpyAsync(&maxm, mx.as<int>() + 1, sizeof maxm, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(&sh_n, row.as<int64_t>() + nv, sizeof sh_n, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    F->sh_n = sh_n;
+    F->sh_vert.reset(room(sh_n, 4), s);
+    F->sh_ptr.reset(room(sh_n + 1, 4), s);
+    F->sh_row.reset(room(nv, 4), s);
+    hipLaunchKernelGGL(k_sh_rows, dim3(grid_of(nv + 1, 256)), dim3(256), 0, s, cnt.as<int32_t>(), rp, nv,
+                       row.as<int64_t>(), ptr.as<int64_t>(), F->sh_vert.as<int32_t>(), F->sh_ptr.as<int32_t>(),
+                       F->sh_row.as<int32_t>());
+    HIPCHK(hipGetLastError());
+    // fixed-width rows of halo places when no vertex has more than 16
+    F->sh_nc = maxm <= 16 ? std::max(1, (maxm + 3) / 4) : 0;
+    if (F->sh_nc > 0) {
+        const int32_t tw = 4 * F->sh_nc;
+        F->sh_tab.reset(room(sh_n * tw, 4), s);
+        if (sh_n > 0) {
+            hipLaunchKernelGGL(k_sh_tab, dim3(grid_of(sh_n * tw, 256)), dim3(256), 0, s, F->sh_ptr.as<int32_t>(),
+                               F->sh_pos.as<int32_t>(), sh_n, tw, F->sh_tab.as<int32_t>());
+            HIPCHK(hipGetLastError());
+        }
+    }
+    F->halo.reset(std::max<size_t>((size_t)nh * 3 * sizeof(double), 8), s);
+    HIPCHK(hipStreamSynchronize(s));   // the scratch above is freed on return
+    F->halo_level = 0;
+    F->blocks_built = true;
+}
+
+}  // namespace ebbx
