@@ -366,17 +366,17 @@ ebbx_status ebbx_implicit_step(ebbx_fem fem, double *d, double *v, const ebbx_st
  * edges relation of a domain holds every ordered vertex pair (i, j) that
  * shares a tet, i == j included, grouped by the tail i and sorted by the head
  * j: row_ptr (nv + 1 int32) and col (n_edges int32), a block-CSR pattern.  It
- * is built on the host from the grouping on first use (synchronous), once per
- * domain, with per-edge lists of the (tet, corner, corner) blocks that sum
- * into it.
+ * is built on first use (synchronous), once per domain, with per-edge lists of
+ * the (tet, corner, corner) blocks that sum into it.
  *
  * ebbx_fem_assemble: K(d) into one 3x3 block per edge, block(i, j)[r][c] =
  * df_{i,r}/dd_{j,c}, the sum over the tets holding i and j, in ascending tet
  * order, of the tet's corner block.  Each tet's 12 x 12 stiffness is computed
  * in FP64 from the same dP as ebbx_fem_Kmul (columns: unit corner
- * displacements); the blocks are stored at the domain's element precision,
- * nine columns of n_edges values.  The library owns a per-tet scratch of
- * 144 FP64 values per tet (about 1.2 KB/tet) and the blocks.  NH tets with
+ * displacements), its blocks rounded to the domain's element precision and
+ * summed in FP64; the sums are stored at the element precision, nine columns
+ * of n_edges values.  The library owns the blocks and, on meshes with a vertex
+ * of several hundred tets, a scratch of 144 values per tet.  NH tets with
  * J <= 0 are counted as by ebbx_fem_forces.  Enqueued on stream (after the
  * synchronous first build). */
 ebbx_status ebbx_fem_assemble(ebbx_fem fem, const double *d, ebbx_stream stream);

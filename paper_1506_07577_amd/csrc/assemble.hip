@@ -7,23 +7,19 @@
 // sorted by the head j, so that the blocks form a block-CSR matrix and K u is
 // a sparse product instead of the matrix-free element map.
 //
-//  - k_elem_matrix: one thread per tet computes the tet's 12 x 12 stiffness in
-//    FP64, column by column (a unit displacement of corner b along axis k gives
-//    dF = e_k (x) grad N_b), with the element maps' own dP, and writes its
-//    sixteen 3x3 corner blocks, rounded to the element precision, to a per-tet
-//    record (the same rounding as the matrix-free map's per-tet corner results,
-//    which are also summed in FP64), one block column at a time through LDS so
-//    that the workgroup writes each tet's four blocks of that column (36
-//    contiguous values) together (per-thread scattered stores of the record
-//    wrote 2.45x its bytes);
-//  - k_edge_gather: one thread per edge sums the corner blocks of the tets
-//    holding both of its vertices in ascending tet order (deterministic) and
-//    stores the edge block at the element precision, nine columns (SoA);
+//  - k_asm_block: a workgroup owns the edges leaving a range of 8 or 4 vertices.  It
+//    evaluates every tet that touches them into a compact record in LDS (the
+//    corner vectors and the symmetric corner products that every 3x3 corner
+//    block of the tet is a short sum of), then one thread per edge sums the
+//    corner blocks of the tets holding both of its vertices in ascending tet
+//    order (deterministic).  No per-tet matrix goes through memory;
+//  - k_elem_matrix and k_edge_gather: the same blocks through a 144-value record
+//    per tet in memory, for meshes with a vertex of so many tets (over 400
+//    neo-Hookean or 240 StVK) that their records do not fit in LDS;
 //  - k_bsr_spmv: sixteen lanes per vertex row; each lane takes edges of the row
 //    (consecutive lanes read consecutive entries of each column) and the row
 //    sum is a fixed butterfly over the sixteen lanes.
 #include <algorithm>
-#include <vector>
 
 #include "fem.h"
 #include "tetmath.h"
@@ -136,6 +132,257 @@ __global__ __launch_bounds__(256) void k_edge_gather(const T *ke, const int32_t 
     for (int q = 0; q < 9; ++q) blocks[(size_t)q * ne + e] = (T)s[q];
 }
 
+
+// ---- blocks straight from the element records, in LDS ------------------------------------------
+
+// A tet's 3x3 corner block (a, b) is a short sum of products of vectors at its corners.  With
+// dF = e_j (x) grad N_b in the models' dP (tetmath.h), and everything scaled by -V0:
+//   neo-Hookean, c_a = F^-T grad N_a:
+//     block[i][j] = s_ab d_ij + p c_b[i] c_a[j] + q c_a[i] c_b[j],
+//     s_ab = mu grad N_a . grad N_b, p = mu - lam ln J, q = lam;
+//   StVK, c_a = F grad N_a:
+//     block[i][j] = s_ab d_ij + m_ab (F F^T)[i][j] + p c_b[i] c_a[j] + q c_a[i] c_b[j],
+//     s_ab = grad N_a . S grad N_b, m_ab = mu grad N_a . grad N_b, p = mu, q = lam.
+// The record holds c (4 x 3), s (10 of the symmetric 4 x 4), p and q, and for StVK m (10) and
+// F F^T (6), all FP64; an odd number of 8-byte entries, so that neighbouring records start in
+// different LDS banks.
+template <int MODEL> struct Rec;
+template <> struct Rec<EBBX_NH> {
+    static constexpr int S = 12, P = 22, Q = 23, M = 0, FF = 0, N = 25;
+};
+template <> struct Rec<EBBX_STVK> {
+    static constexpr int S = 12, P = 22, Q = 23, M = 24, FF = 34, N = 41;
+};
+
+// place of (a, b) among the 10 entries of a symmetric 4 x 4: the diagonal first, then (0, 1),
+// (0, 2), (0, 3), (1, 2), (1, 3), (2, 3); the same from a table of 4-bit places
+constexpr int sym4_at(int a, int b) {
+    return a == b ? a : 4 + (a < b ? a * (7 - a) / 2 + b - a - 1 : b * (7 - b) / 2 + a - b - 1);
+}
+__device__ __forceinline__ uint32_t sym4(uint32_t a, uint32_t b) {
+    return (uint32_t)(0x3986927587146540ull >> (16u * a + 4u * b)) & 15u;
+}
+// and of (i, j) among the 6 of a symmetric 3 x 3
+__host__ __device__ constexpr int sym3(int i, int j) { return i <= j ? i * (5 - i) / 2 + j : j * (5 - j) / 2 + i; }
+
+constexpr int AB_THREADS = 192;         // k_asm_block: AB_OFF threads on off-diagonal blocks, the others on diagonal ones
+constexpr int AB_OFF = 128;
+constexpr int TB_THREADS = 256;         // table construction
+constexpr int AB_MAXINC = 4096;          // incidences of one workgroup's vertices (table construction)
+constexpr size_t AB_LDS = 80 * 1024;     // most LDS of one workgroup: two workgroups per CU
+
+// LDS of a workgroup with at most `tets` records and the entries of `inc` incidences (4 each)
+size_t asm_lds(int32_t model, int64_t tets, int64_t inc) {
+    return (size_t)(model == EBBX_NH ? Rec<EBBX_NH>::N : Rec<EBBX_STVK>::N) * (size_t)tets * sizeof(double) +
+           (size_t)(4 * inc) * sizeof(uint16_t);
+}
+
+struct AsmBlockArgs {
+    AsmArgs m;
+    uint32_t nv, ne, vb, most;           // vb: owned vertices per workgroup, most: tets of the largest
+    const int32_t *row, *gptr;           // edges of vertex i: [row[i], row[i+1]); entries of edge e: [gptr[e], gptr[e+1])
+    const uint16_t *ent;                 // 16 (tet's place in the workgroup's list) + 4 a + b
+    const int32_t *tptr, *tets;          // workgroup's tets, ascending
+    const int4 *keys;                    // their corners
+    const int32_t *diag;                 // vertex's own edge (i, i), -1 if it has no tet
+    void *blocks;
+};
+
+template <class T, int MODEL>
+__device__ __forceinline__ bool tet_record(const AsmArgs &a, uint32_t t, int4 key, double *s) {
+    using R = Rec<MODEL>;
+    double b[9], G[9], gb[4][3];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) b[k] = (double)ldc<T>(a.B[k], t);
+    const double V0 = tet_V0(b);
+    const double mu = a.mu_t ? (double)ldc<T>(a.mu_t, t) : a.mu;
+    const double lam = a.lam_t ? (double)ldc<T>(a.lam_t, t) : a.lam;
+    {
+        const uint32_t v[4] = {(uint32_t)key.x, (uint32_t)key.y, (uint32_t)key.z, (uint32_t)key.w};
+        double qd[4][3];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) qd[c][k] = ldc<double>(a.d[k], v[c]);
+        grad_from(qd, b, G);
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        gb[1][j] = b[j];
+        gb[2][j] = b[3 + j];
+        gb[3][j] = b[6 + j];
+        gb[0][j] = -(b[j] + b[3 + j] + b[6 + j]);
+    }
+    bool ok = true;
+    if (MODEL == EBBX_NH) {
+        const double jm1 = jm1_of(G), J = 1.0 + jm1, iJ = t_rcp(J), lnJ = t_log1p(jm1);
+        double C[9];
+        cof_IpG(G, C);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                s[3 * c + i] = iJ * (C[3 * i] * gb[c][0] + C[3 * i + 1] * gb[c][1] + C[3 * i + 2] * gb[c][2]);
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int y = x; y < 4; ++y)
+                s[R::S + sym4_at(x, y)] =
+                    -V0 * mu * (gb[x][0] * gb[y][0] + gb[x][1] * gb[y][1] + gb[x][2] * gb[y][2]);
+        s[R::P] = -V0 * (mu - lam * lnJ);
+        s[R::Q] = -V0 * lam;
+        ok = J > 0.0;
+    } else {
+        double S[9];
+        stvk_S(mu, lam, G, -V0, S);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                s[3 * c + i] =
+                    gb[c][i] + (G[3 * i] * gb[c][0] + G[3 * i + 1] * gb[c][1] + G[3 * i + 2] * gb[c][2]);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            double Sx[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) Sx[i] = S[3 * i] * gb[x][0] + S[3 * i + 1] * gb[x][1] + S[3 * i + 2] * gb[x][2];
+#pragma unroll
+            for (int y = x; y < 4; ++y) {
+                s[R::S + sym4_at(x, y)] = Sx[0] * gb[y][0] + Sx[1] * gb[y][1] + Sx[2] * gb[y][2];
+                s[R::M + sym4_at(x, y)] =
+                    -V0 * mu * (gb[x][0] * gb[y][0] + gb[x][1] * gb[y][1] + gb[x][2] * gb[y][2]);
+            }
+        }
+        double F[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) F[k] = G[k] + (k % 4 == 0 ? 1.0 : 0.0);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = i; j < 3; ++j)
+                s[R::FF + sym3(i, j)] = F[3 * i] * F[3 * j] + F[3 * i + 1] * F[3 * j + 1] + F[3 * i + 2] * F[3 * j + 2];
+        s[R::P] = -V0 * mu;
+        s[R::Q] = -V0 * lam;
+    }
+    return ok;
+}
+
+// Bound by FP64 issue and LDS reads at the two to five workgroups per CU that the records leave
+// LDS for; the blocks' write alone takes 27 us where the kernel takes 178 to 283.  Each tet is
+// evaluated by every workgroup that owns one of its vertices, about three times on these meshes.
+// Vertices per workgroup, 890k Morton-ordered tets, FP64: neo-Hookean 249 / 178 / 205 us and StVK
+// 459 / 302 / 283 us for 16 / 8 / 4: fewer evaluations against more workgroups in flight, and
+// StVK's records are the larger.  The records alone take 85 (neo-Hookean) and 125 us (StVK) of
+// that.  128 and 256 threads measured 291 and 278 us (StVK), 200 and 176 us (neo-Hookean).  The two
+// kernels above, through 1 GB of per-tet matrices, took 777 us (StVK).
+template <class T, int MODEL>
+__global__ __launch_bounds__(AB_THREADS) void k_asm_block(AsmBlockArgs a) {
+    extern __shared__ double s_rec[];
+    using R = Rec<MODEL>;
+    const uint32_t tid = threadIdx.x;
+    uint16_t *s_ent = (uint16_t *)(s_rec + R::N * a.most);
+    const uint32_t wg = xcd_block(blockIdx.x, gridDim.x);
+    const uint32_t v0 = wg * a.vb, v1 = min(v0 + a.vb, a.nv);
+    const int32_t t0 = a.tptr[wg], nt = a.tptr[wg + 1] - t0;
+    const uint32_t e0 = (uint32_t)a.row[v0], e1 = (uint32_t)a.row[v1];
+    const int32_t g0 = a.gptr[e0], g1 = a.gptr[e1];
+    // AB_OFF threads sum off-diagonal blocks, one edge each, the others diagonal blocks, one of the
+    // six entries each; the first one's place is loaded ahead of the records
+    const bool off = tid < AB_OFF;
+    const uint32_t lt = off ? tid : tid - AB_OFF;
+    int32_t e = -1, j0 = 0, j1 = 0;
+    if (off) {
+        if (e0 + lt < e1) e = (int32_t)(e0 + lt);
+    } else if (lt < 6 * (v1 - v0)) {
+        e = a.diag[v0 + lt / 6];
+    }
+    if (e >= 0) {
+        j0 = a.gptr[e];
+        j1 = a.gptr[e + 1];
+    }
+    for (int32_t j = (int32_t)tid; j < g1 - g0; j += AB_THREADS) s_ent[j] = a.ent[g0 + j];
+    for (int32_t i = (int32_t)tid; i < nt; i += AB_THREADS) {
+        const int4 key = a.keys[t0 + i];
+        const uint32_t t = (uint32_t)a.tets[t0 + i];
+        const bool ok = tet_record<T, MODEL>(a.m, t, key, s_rec + R::N * i);
+        // an inverted tet is counted once, by the workgroup that owns corner 0
+        if (MODEL == EBBX_NH && !ok && (uint32_t)key.x >= v0 && (uint32_t)key.x < v1)
+            atomicAdd(a.m.n_inv + (a.m.tmesh ? a.m.tmesh[t] : 0), 1ull);
+    }
+    __syncthreads();
+    T *out = (T *)a.blocks;
+    if (off) {
+        for (uint32_t at = e0 + lt; at < e1; at += AB_OFF) {
+            if (at != e0 + lt) {
+                j0 = a.gptr[at];
+                j1 = a.gptr[at + 1];
+            }
+            const uint32_t first = s_ent[j0 - g0];
+            if (((first >> 2) & 3u) == (first & 3u)) continue;   // a diagonal block
+            double acc[9];
+#pragma unroll
+            for (int k = 0; k < 9; ++k) acc[k] = 0.0;
+#pragma unroll 2
+            for (int32_t j = j0 - g0; j < j1 - g0; ++j) {
+                const uint32_t c = s_ent[j], ca = (c >> 2) & 3u, cb = c & 3u, ab = sym4(ca, cb);
+                const double *r = s_rec + R::N * (c >> 4);
+                const double p = r[R::P], q = r[R::Q], sab = r[R::S + ab];
+                const double mab = MODEL == EBBX_STVK ? r[R::M + ab] : 0.0;
+                double x[3], y[3], u[3], w[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    x[i] = r[3 * ca + i];
+                    y[i] = r[3 * cb + i];
+                    u[i] = p * y[i];
+                    w[i] = q * x[i];
+                }
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        // rounded to the element precision, summed in FP64
+                        double v = sizeof(T) == 8 ? acc[3 * i + k] : 0.0;
+                        if (i == k) v += sab;
+                        if (MODEL == EBBX_STVK) v += mab * r[R::FF + sym3(i, k)];
+                        v += u[i] * x[k];
+                        v += w[i] * y[k];
+                        if (sizeof(T) == 8) acc[3 * i + k] = v;
+                        else acc[3 * i + k] += (double)(T)v;
+                    }
+            }
+#pragma unroll
+            for (int k = 0; k < 9; ++k) out[(size_t)k * a.ne + at] = (T)acc[k];
+        }
+    } else {
+        for (uint32_t w = lt; w < 6 * (v1 - v0); w += AB_THREADS - AB_OFF) {
+            if (w != lt) {
+                e = a.diag[v0 + w / 6];
+                if (e >= 0) {
+                    j0 = a.gptr[e];
+                    j1 = a.gptr[e + 1];
+                }
+            }
+            if (e < 0) continue;   // a vertex with no tet
+            const uint32_t kf = w % 6u, i = kf < 3 ? 0u : kf < 5 ? 1u : 2u, l = kf < 3 ? kf : kf < 5 ? kf - 2u : 2u;
+            const uint32_t f = R::FF + kf;
+            double acc = 0.0;
+#pragma unroll 4
+            for (int32_t j = j0 - g0; j < j1 - g0; ++j) {
+                const uint32_t c = s_ent[j], ca = c & 3u;
+                const double *r = s_rec + R::N * (c >> 4);
+                double v = sizeof(T) == 8 ? acc : 0.0;
+                if (i == l) v += r[R::S + ca];
+                if (MODEL == EBBX_STVK) v += r[R::M + ca] * r[f];
+                v += (r[R::P] + r[R::Q]) * r[3 * ca + i] * r[3 * ca + l];
+                if (sizeof(T) == 8) acc = v;
+                else acc += (double)(T)v;
+            }
+            out[(size_t)(3 * i + l) * a.ne + e] = (T)acc;
+            if (i != l) out[(size_t)(3 * l + i) * a.ne + e] = (T)acc;
+        }
+    }
+}
+
 template <class T> struct BsrArgs {
     const int32_t *row, *col;
     const T *k[9];
@@ -182,93 +429,283 @@ unsigned grid_of(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
 }  // namespace
 
-// Edges relation and gather lists, from the grouping (vertex -> (tet, corner)
-// incidences in tet order).  Host side, once per domain.
+// ---- tables, on the device ---------------------------------------------------------------------
+
+namespace {
+
+// Entry 16 t + 4 a + b is corner block (a, b) of tet t; its key orders the edges (tail, head).
+__global__ void k_edge_keys(const int32_t *keys, int64_t nt, int shift, uint64_t *key, uint32_t *val) {
+    const int64_t n = 16 * nt;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t t = i >> 4;
+        const int a = (int)(i >> 2) & 3, b = (int)i & 3;
+        key[i] = ((uint64_t)(uint32_t)keys[a * nt + t] << shift) | (uint32_t)keys[b * nt + t];
+        val[i] = (uint32_t)i;
+    }
+}
+
+__global__ void k_edge_heads(const uint64_t *key, int64_t n, int64_t *flag) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= n; i += (int64_t)gridDim.x * blockDim.x)
+        flag[i] = i < n && (i == 0 || key[i] != key[i - 1]);
+}
+
+// at[i]: edges before entry i.  The first entry of an edge writes its head and its entries' start;
+// the first entry of a tail also the row offsets up to that tail, the last entry those after it.
+__global__ void k_edge_fill(const uint64_t *key, const int64_t *at, int64_t n, int64_t nv, int shift, int32_t *row,
+                            int32_t *col, int32_t *gptr) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const uint64_t k = key[i];
+        const int64_t tail = (int64_t)(k >> shift), before = i > 0 ? (int64_t)(key[i - 1] >> shift) : -1;
+        if (at[i + 1] != at[i]) {
+            col[at[i]] = (int32_t)(k & ((1ull << shift) - 1ull));
+            gptr[at[i]] = (int32_t)i;
+        }
+        for (int64_t v = before + 1; v <= tail; ++v) row[v] = (int32_t)at[i];
+        if (i == n - 1) {
+            for (int64_t v = tail + 1; v <= nv; ++v) row[v] = (int32_t)at[n];
+            gptr[at[n]] = (int32_t)n;
+        }
+    }
+}
+
+// The distinct tets of vertices [v0, v1), sorted ascending into s[0, *nu); false if they have
+// more than AB_MAXINC incidences.
+__device__ __forceinline__ bool tets_of(const int64_t *rp, const int32_t *inc, int64_t v0, int64_t v1, uint32_t *s,
+                                        int32_t *s_n, int32_t *nu) {
+    const int64_t p0 = rp[v0], ninc = rp[v1] - p0;
+    if (ninc > AB_MAXINC) return false;
+    int32_t n = 64;
+    while (n < ninc) n <<= 1;
+    for (int32_t i = threadIdx.x; i < n; i += TB_THREADS) s[i] = i < ninc ? (uint32_t)inc[p0 + i] >> 2 : ~0u;
+    __syncthreads();
+    for (int32_t k = 2; k <= n; k <<= 1)
+        for (int32_t j = k >> 1; j > 0; j >>= 1) {
+            for (int32_t e = threadIdx.x; e < n / 2; e += TB_THREADS) {
+                const int32_t i = ((e & ~(j - 1)) << 1) | (e & (j - 1)), o = i | j;
+                const uint32_t x = s[i], y = s[o];
+                if ((x > y) == ((i & k) == 0)) {
+                    s[i] = y;
+                    s[o] = x;
+                }
+            }
+            __syncthreads();
+        }
+    // compact in place: every thread reads its stretch before any writes
+    const int32_t per = (n + TB_THREADS - 1) / TB_THREADS, i0 = (int32_t)threadIdx.x * per;
+    uint32_t keep[AB_MAXINC / TB_THREADS];
+    int32_t m = 0;
+#pragma unroll
+    for (int32_t u = 0; u < AB_MAXINC / TB_THREADS; ++u) {
+        const int32_t i = i0 + u;
+        keep[u] = ~0u;
+        if (u < per && i < n && s[i] != ~0u && (i == 0 || s[i] != s[i - 1])) {
+            keep[u] = s[i];
+            ++m;
+        }
+    }
+    s_n[threadIdx.x] = m;
+    __syncthreads();
+    int32_t at = 0, total = 0;
+    for (int32_t w = 0; w < TB_THREADS; ++w) {
+        if (w < (int32_t)threadIdx.x) at += s_n[w];
+        total += s_n[w];
+    }
+#pragma unroll
+    for (int32_t u = 0; u < AB_MAXINC / TB_THREADS; ++u)
+        if (keep[u] != ~0u) s[at++] = keep[u];
+    __syncthreads();
+    *nu = total;
+    return true;
+}
+
+// Tets per workgroup of vb vertices into count[wg], the most tets and incidences of any into most[].
+__global__ __launch_bounds__(TB_THREADS) void k_asm_count(const int64_t *rp, const int32_t *inc, int64_t nv, int32_t vb,
+                                                          int64_t *count, int *most) {
+    __shared__ uint32_t s[AB_MAXINC];
+    __shared__ int32_t s_n[TB_THREADS];
+    const int64_t v0 = (int64_t)blockIdx.x * vb, v1 = v0 + vb < nv ? v0 + vb : nv;
+    int32_t nu = 0;
+    const bool fits = tets_of(rp, inc, v0, v1, s, s_n, &nu);   // uniform over the workgroup
+    if (threadIdx.x == 0) {
+        count[blockIdx.x] = fits ? nu : 0;
+        atomicMax(most, fits ? nu : 1 << 30);
+        atomicMax(most + 1, fits ? (int)(rp[v1] - rp[v0]) : 0);
+    }
+}
+
+// The workgroups' tet lists, and each entry of their edges as a place in its workgroup's list.
+__global__ __launch_bounds__(TB_THREADS) void k_asm_fill(const int64_t *rp, const int32_t *inc, int64_t nv, int32_t vb,
+                                                         const int64_t *base, const int32_t *row, const int32_t *gptr,
+                                                         const uint32_t *gent, const int32_t *keys, int64_t nt,
+                                                         int32_t *tptr, int32_t *tets, int4 *tkeys, int32_t *diag,
+                                                         uint16_t *ent) {
+    __shared__ uint32_t s[AB_MAXINC];
+    __shared__ int32_t s_n[TB_THREADS];
+    const int64_t v0 = (int64_t)blockIdx.x * vb, v1 = v0 + vb < nv ? v0 + vb : nv;
+    int32_t nu = 0;
+    if (!tets_of(rp, inc, v0, v1, s, s_n, &nu)) return;
+    const int64_t t0 = base[blockIdx.x];
+    if (threadIdx.x == 0) {
+        tptr[blockIdx.x] = (int32_t)t0;
+        if (v1 == nv) tptr[blockIdx.x + 1] = (int32_t)(t0 + nu);
+    }
+    for (int32_t i = threadIdx.x; i < nu; i += TB_THREADS) {
+        const int64_t t = s[i];
+        tets[t0 + i] = (int32_t)t;
+        tkeys[t0 + i] = make_int4(keys[t], keys[nt + t], keys[2 * nt + t], keys[3 * nt + t]);
+    }
+    for (int64_t v = v0 + threadIdx.x; v < v1; v += TB_THREADS) {
+        int32_t own = -1;   // the edge whose entries have equal corners
+        for (int32_t e = row[v]; e < row[v + 1]; ++e) {
+            const uint32_t c = gent[gptr[e]];
+            if (((c >> 2) & 3u) == (c & 3u)) own = e;
+        }
+        diag[v] = own;
+    }
+    for (int32_t p = gptr[row[v0]] + (int32_t)threadIdx.x; p < gptr[row[v1]]; p += TB_THREADS) {
+        const uint32_t c = gent[p], t = c >> 4;
+        int32_t lo = 0, hi = nu - 1;
+        while (lo < hi) {
+            const int32_t mid = (lo + hi) >> 1;
+            if (s[mid] < t) lo = mid + 1;
+            else hi = mid;
+        }
+        ent[p] = (uint16_t)(((uint32_t)lo << 4) | (c & 15u));
+    }
+}
+
+}  // namespace
+
+// The edges relation and the entry lists from the grouping's keys: the 16 nt corner blocks sorted
+// by (tail, head), stably, so that an edge's entries ascend in (tet, corner, corner); then the
+// workgroups' tables of k_asm_block: 8 vertices per workgroup (neo-Hookean) or 4 (StVK), measured
+// at the kernel, or as many fewer as the LDS takes.  Once per domain, synchronous.
 void build_edges(ebbx_fem_s *F, hipStream_t s) {
     if (F->n_edges >= 0) return;
-    const int64_t nt = F->nt, nv = F->nv;
-    if (nt >= (int64_t(1) << 28)) fail(EBBX_E_ARG, "assembled stiffness: at most 2^28 tets");
-    std::vector<int32_t> keys((size_t)(4 * nt));
-    if (nt > 0) HIPCHK(hipMemcpy(keys.data(), F->keys, keys.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-    std::vector<int64_t> rp((size_t)(nv + 1));
-    HIPCHK(hipMemcpy(rp.data(), F->group->row_ptr.get(), rp.size() * sizeof(int64_t), hipMemcpyDeviceToHost));
-    std::vector<int32_t> inc((size_t)std::max<int64_t>(4 * nt, 1));
-    if (nt > 0) HIPCHK(hipMemcpy(inc.data(), F->group->inc.get(), (size_t)(4 * nt) * sizeof(int32_t),
-                                 hipMemcpyDeviceToHost));
-    std::vector<int32_t> row((size_t)(nv + 1), 0), col, gptr(1, 0);
-    std::vector<uint32_t> gent;
-    col.reserve((size_t)(16 * nv + 16));
-    gent.reserve((size_t)(16 * nt));
-    struct Ent {
-        int32_t j;
-        uint32_t code;   // 16 t + 4 a + b
-    };
-    std::vector<Ent> buf;
-    for (int64_t i = 0; i < nv; ++i) {
-        buf.clear();
-        for (int64_t p = rp[(size_t)i]; p < rp[(size_t)i + 1]; ++p) {
-            const uint32_t t = (uint32_t)inc[(size_t)p] >> 2, ca = (uint32_t)inc[(size_t)p] & 3u;
-            for (uint32_t cb = 0; cb < 4; ++cb)
-                buf.push_back({keys[(size_t)cb * nt + t], 16u * t + 4u * ca + cb});
-        }
-        std::sort(buf.begin(), buf.end(), [](const Ent &x, const Ent &y) {
-            return x.j != y.j ? x.j < y.j : x.code < y.code;
-        });
-        for (size_t k = 0; k < buf.size(); ++k) {
-            if (k == 0 || buf[k].j != buf[k - 1].j) {
-                if (k > 0) gptr.push_back((int32_t)gent.size());
-                col.push_back(buf[k].j);
-            }
-            gent.push_back(buf[k].code);
-        }
-        if (!buf.empty()) gptr.push_back((int32_t)gent.size());
-        row[(size_t)i + 1] = (int32_t)col.size();
+    const int64_t nt = F->nt, nv = F->nv, n = 16 * nt;
+    if (nt >= (int64_t(1) << 27)) fail(EBBX_E_ARG, "assembled stiffness: at most 2^27 tets");
+    int shift = 1;
+    while ((int64_t(1) << shift) < nv) ++shift;
+    auto room = [](int64_t count, size_t each) { return std::max<size_t>((size_t)count * each, 16); };
+    auto grid = [](int64_t m) { return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((m + 255) / 256, 65536))); };
+    F->e_row.reset(room(nv + 1, 4), s);
+    F->e_gent.reset(room(n, 4), s);
+    int64_t ne = 0;
+    if (nt > 0) {
+        DevBuf key(room(n, 8), s), at(room(n + 1, 8), s);
+        hipLaunchKernelGGL(k_edge_keys, grid(n), dim3(256), 0, s, F->keys, nt, shift, key.as<uint64_t>(),
+                           F->e_gent.as<uint32_t>());
+        HIPCHK(hipGetLastError());
+        radix_sort_pairs_u64(key.as<uint64_t>(), F->e_gent.as<uint32_t>(), n, 2 * shift, s);
+        hipLaunchKernelGGL(k_edge_heads, grid(n + 1), dim3(256), 0, s, key.as<uint64_t>(), n, at.as<int64_t>());
+        HIPCHK(hipGetLastError());
+        exclusive_scan_i64(at.as<int64_t>(), n + 1, s);
+        HIPCHK(hipMemcpyAsync(&ne, at.as<int64_t>() + n, sizeof ne, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        F->e_col.reset(room(ne, 4), s);
+        F->e_gptr.reset(room(ne + 1, 4), s);
+        hipLaunchKernelGGL(k_edge_fill, grid(n), dim3(256), 0, s, key.as<uint64_t>(), at.as<int64_t>(), n, nv, shift,
+                           F->e_row.as<int32_t>(), F->e_col.as<int32_t>(), F->e_gptr.as<int32_t>());
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipStreamSynchronize(s));
+    } else {
+        F->e_col.reset(room(0, 4), s);
+        F->e_gptr.reset(room(1, 4), s);
+        HIPCHK(hipMemsetAsync(F->e_row.get(), 0, F->e_row.bytes(), s));
+        HIPCHK(hipMemsetAsync(F->e_gptr.get(), 0, F->e_gptr.bytes(), s));
     }
-    if (col.size() >= (size_t)(1u << 31)) fail(EBBX_E_ARG, "assembled stiffness: too many edges");
-    F->n_edges = (int64_t)col.size();
-    auto up = [&](DevBuf &dst, const void *src, size_t bytes) {
-        dst.reset(std::max<size_t>(bytes, 8), s);
-        if (bytes) HIPCHK(hipMemcpy(dst.get(), src, bytes, hipMemcpyHostToDevice));
-    };
-    up(F->e_row, row.data(), row.size() * sizeof(int32_t));
-    up(F->e_col, col.data(), col.size() * sizeof(int32_t));
-    up(F->e_gptr, gptr.data(), gptr.size() * sizeof(int32_t));
-    up(F->e_gent, gent.data(), gent.size() * sizeof(uint32_t));
+    F->a_vb = 0;
+    const int64_t *rp = F->group->row_ptr.as<int64_t>();
+    const int32_t *inc = F->group->inc.as<int32_t>();
+    for (int32_t vb = F->model == EBBX_NH ? 8 : 4; vb >= 1 && ne > 0 && !F->a_vb; vb /= 2) {
+        const int64_t nwg = (nv + vb - 1) / vb;
+        DevBuf base(room(nwg + 1, 8), s), mx(16, s);
+        HIPCHK(hipMemsetAsync(mx.get(), 0, 2 * sizeof(int), s));
+        HIPCHK(hipMemsetAsync(base.get(), 0, base.bytes(), s));
+        hipLaunchKernelGGL(k_asm_count, dim3((unsigned)nwg), dim3(TB_THREADS), 0, s, rp, inc, nv, vb,
+                           base.as<int64_t>(), mx.as<int>());
+        HIPCHK(hipGetLastError());
+        exclusive_scan_i64(base.as<int64_t>(), nwg + 1, s);
+        int most[2] = {0, 0};
+        int64_t total = 0;
+        HIPCHK(hipMemcpyAsync(most, mx.get(), sizeof most, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipMemcpyAsync(&total, base.as<int64_t>() + nwg, sizeof total, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        if (asm_lds(F->model, most[0], most[1]) > AB_LDS || total >= (int64_t(1) << 31)) continue;
+        F->a_tptr.reset(room(nwg + 1, 4), s);
+        F->a_tets.reset(room(total, 4), s);
+        F->a_keys.reset(room(total, 16), s);
+        F->a_diag.reset(room(nv, 4), s);
+        F->a_ent.reset(room(n, 2), s);
+        hipLaunchKernelGGL(k_asm_fill, dim3((unsigned)nwg), dim3(TB_THREADS), 0, s, rp, inc, nv, vb,
+                           base.as<int64_t>(), F->e_row.as<int32_t>(), F->e_gptr.as<int32_t>(),
+                           F->e_gent.as<uint32_t>(), F->keys, nt, F->a_tptr.as<int32_t>(),
+                           F->a_tets.as<int32_t>(), F->a_keys.as<int4>(), F->a_diag.as<int32_t>(),
+                           F->a_ent.as<uint16_t>());
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipStreamSynchronize(s));
+        F->e_gent.release();
+        F->a_most = most[0];
+        F->a_inc = most[1];
+        F->a_vb = vb;
+    }
+    HIPCHK(hipStreamSynchronize(s));
+    F->n_edges = ne;
 }
 
 namespace {
 
 template <class T> void launch_assemble(ebbx_fem_s *F, const double *d, hipStream_t s) {
-    const int64_t nt = F->nt, nv = F->nv;
+    const int64_t nt = F->nt, nv = F->nv, ne = F->n_edges;
     const size_t es = sizeof(T);
-    if (nt > 0) {
-        AsmArgs a{};
-        a.nt = (uint32_t)nt;
-        for (int c = 0; c < 4; ++c) a.key[c] = F->keys + (size_t)c * nt;
-        for (int k = 0; k < 9; ++k) a.B[k] = (const char *)F->B.get() + (size_t)k * nt * es;
-        if (F->per_tet) {
-            a.mu_t = F->mat.get();
-            a.lam_t = (const char *)F->mat.get() + (size_t)nt * es;
-        }
-        a.mu = F->mu;
-        a.lam = F->lam;
-        for (int k = 0; k < 3; ++k) a.d[k] = d + (size_t)k * nv;
-        a.ke = F->e_ke.get();
-        a.n_inv = F->status.as<unsigned long long>();
-        a.tmesh = F->tmesh;
+    if (ne == 0) return;
+    AsmArgs a{};
+    a.nt = (uint32_t)nt;
+    for (int c = 0; c < 4; ++c) a.key[c] = F->keys + (size_t)c * nt;
+    for (int k = 0; k < 9; ++k) a.B[k] = (const char *)F->B.get() + (size_t)k * nt * es;
+    if (F->per_tet) {
+        a.mu_t = F->mat.get();
+        a.lam_t = (const char *)F->mat.get() + (size_t)nt * es;
+    }
+    a.mu = F->mu;
+    a.lam = F->lam;
+    for (int k = 0; k < 3; ++k) a.d[k] = d + (size_t)k * nv;
+    a.ke = F->e_ke.get();
+    a.n_inv = F->status.as<unsigned long long>();
+    a.tmesh = F->tmesh;
+    if (F->a_vb) {
+        AsmBlockArgs b{};
+        b.m = a;
+        b.nv = (uint32_t)nv;
+        b.ne = (uint32_t)ne;
+        b.vb = (uint32_t)F->a_vb;
+        b.most = (uint32_t)F->a_most;
+        b.row = F->e_row.as<int32_t>();
+        b.gptr = F->e_gptr.as<int32_t>();
+        b.ent = F->a_ent.as<uint16_t>();
+        b.tptr = F->a_tptr.as<int32_t>();
+        b.tets = F->a_tets.as<int32_t>();
+        b.keys = F->a_keys.as<int4>();
+        b.diag = F->a_diag.as<int32_t>();
+        b.blocks = F->e_blocks.get();
+        const dim3 g(grid_of(nv, F->a_vb));
         if (F->model == EBBX_STVK)
-            hipLaunchKernelGGL((k_elem_matrix<T, EBBX_STVK>), dim3(grid_of(nt, EM_THREADS)), dim3(EM_THREADS), 0, s, a);
+            hipLaunchKernelGGL((k_asm_block<T, EBBX_STVK>), g, dim3(AB_THREADS),
+                               asm_lds(F->model, F->a_most, F->a_inc), s, b);
         else
-            hipLaunchKernelGGL((k_elem_matrix<T, EBBX_NH>), dim3(grid_of(nt, EM_THREADS)), dim3(EM_THREADS), 0, s, a);
+            hipLaunchKernelGGL((k_asm_block<T, EBBX_NH>), g, dim3(AB_THREADS),
+                               asm_lds(F->model, F->a_most, F->a_inc), s, b);
         HIPCHK(hipGetLastError());
+        return;
     }
-    const int64_t ne = F->n_edges;
-    if (ne > 0) {
-        hipLaunchKernelGGL((k_edge_gather<T>), dim3(grid_of(ne, 256)), dim3(256), 0, s,
-                           (const T *)F->e_ke.get(), F->e_gptr.as<int32_t>(), F->e_gent.as<uint32_t>(),
-                           (uint32_t)ne, F->e_blocks.as<T>());
-        HIPCHK(hipGetLastError());
-    }
+    if (F->model == EBBX_STVK)
+        hipLaunchKernelGGL((k_elem_matrix<T, EBBX_STVK>), dim3(grid_of(nt, EM_THREADS)), dim3(EM_THREADS), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_elem_matrix<T, EBBX_NH>), dim3(grid_of(nt, EM_THREADS)), dim3(EM_THREADS), 0, s, a);
+    HIPCHK(hipGetLastError());
+    hipLaunchKernelGGL((k_edge_gather<T>), dim3(grid_of(ne, 256)), dim3(256), 0, s, (const T *)F->e_ke.get(),
+                       F->e_gptr.as<int32_t>(), F->e_gent.as<uint32_t>(), (uint32_t)ne, F->e_blocks.as<T>());
+    HIPCHK(hipGetLastError());
 }
 
 template <class T> void launch_spmv(ebbx_fem_s *F, const double *u, double *y, int accumulate, hipStream_t s) {
@@ -291,9 +728,9 @@ template <class T> void launch_spmv(ebbx_fem_s *F, const double *u, double *y, i
 
 void assemble_stiffness(ebbx_fem_s *F, const double *d, hipStream_t s) {
     build_edges(F, s);
-    // the blocks and the per-tet scratch, on the first assembly
+    // the blocks, and where the LDS does not take the records the per-tet scratch, on the first assembly
     const size_t blk_bytes = std::max<size_t>((size_t)9 * F->n_edges * F->esize, 8);
-    const size_t ke_bytes = std::max<size_t>((size_t)F->nt * 144 * F->esize, 8);
+    const size_t ke_bytes = F->a_vb ? 0 : std::max<size_t>((size_t)F->nt * 144 * F->esize, 8);
     if (F->e_blocks.bytes() != blk_bytes) F->e_blocks.reset(blk_bytes, s);
     if (F->e_ke.bytes() != ke_bytes) F->e_ke.reset(ke_bytes, s);
     if (F->prec == EBBX_F32) launch_assemble<float>(F, d, s);

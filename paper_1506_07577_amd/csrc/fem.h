@@ -270,6 +270,10 @@ struct ebbx_fem_s {
     int64_t n_edges = -1;      // -1: not built
     bool assembled = false;    // e_blocks holds K(d) of an ebbx_fem_assemble call
     ebbx::DevBuf e_row, e_col, e_gptr, e_gent, e_blocks, e_ke;
+    // k_asm_block: vertices per workgroup (0: the path through memory), the most tets and incidences
+    // of one, tables
+    int32_t a_vb = 0, a_most = 0, a_inc = 0;
+    ebbx::DevBuf a_tptr, a_tets, a_keys, a_diag, a_ent;
 
     // implicit-step state (allocated on first step)
     struct Step;
