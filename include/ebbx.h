@@ -165,7 +165,11 @@ enum { EBBX_STVK = 0, EBBX_NH = 1 };
  *   ATOMIC:    FP64 hardware atomics, one per (tet, corner, component);
  *   SEG:       per-corner partials, then a vertex-owned sum over the grouping's
  *              incidence in fixed order (bitwise deterministic);
- *   BLOCK:     consecutive tets form blocks (best after Morton reordering);
+ *   BLOCK:     consecutive tets form blocks (best after Morton reordering; where
+ *              the rows' order has so little locality that a block touches more
+ *              than 256 vertices, the tables may take the tets in a locality
+ *              order of their own, which no result but the order of the sums
+ *              depends on);
  *              a block stages its vertices' fields in LDS, writes each tet
  *              corner's result to its row of the block's precomputed incidence
  *              order, sums each vertex's contiguous rows in fixed order,

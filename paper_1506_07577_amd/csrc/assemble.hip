@@ -583,7 +583,7 @@ __global__ __launch_bounds__(TB_THREADS) void k_asm_fill(const int64_t *rp, cons
 void build_edges(ebbx_fem_s *F, hipStream_t s) {
     if (F->n_edges >= 0) return;
     const int64_t nt = F->nt, nv = F->nv, n = 16 * nt;
-    if (nt >= (int64_t(1) << 27)) fail(EBBX_E_ARG, "assembled stiffness: at most 2^27 tets");
+    if (nt >= (int64_t(1) << 28)) fail(EBBX_E_ARG, "assembled stiffness: at most 2^28 tets");
     int shift = 1;
     while ((int64_t(1) << shift) < nv) ++shift;
     auto room = [](int64_t count, size_t each) { return std::max<size_t>((size_t)count * each, 16); };
@@ -617,7 +617,7 @@ void build_edges(ebbx_fem_s *F, hipStream_t s) {
     F->a_vb = 0;
     const int64_t *rp = F->group->row_ptr.as<int64_t>();
     const int32_t *inc = F->group->inc.as<int32_t>();
-    for (int32_t vb = F->model == EBBX_NH ? 8 : 4; vb >= 1 && ne > 0 && !F->a_vb; vb /= 2) {
+    for (int32_t vb = F->model == EBBX_NH ? 8 : 4; vb >= 1 && ne > 0 && n < (int64_t(1) << 31) && !F->a_vb; vb /= 2) {
         const int64_t nwg = (nv + vb - 1) / vb;
         DevBuf base(room(nwg + 1, 8), s), mx(16, s);
         HIPCHK(hipMemsetAsync(mx.get(), 0, 2 * sizeof(int), s));
@@ -727,6 +727,7 @@ template <class T> void launch_spmv(ebbx_fem_s *F, const double *u, double *y, i
 }  // namespace
 
 void assemble_stiffness(ebbx_fem_s *F, const double *d, hipStream_t s) {
+    if (F->nt >= (int64_t(1) << 27)) fail(EBBX_E_ARG, "assembled stiffness: at most 2^27 tets");   // 32-bit entry lists
     build_edges(F, s);
     // the blocks, and where the LDS does not take the records the per-tet scratch, on the first assembly
     const size_t blk_bytes = std::max<size_t>((size_t)9 * F->n_edges * F->esize, 8);

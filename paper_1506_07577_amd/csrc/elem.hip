@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void k_elem(ElemArgs a) {
 // else 2 x 16 bits in each of two words).
 
 template <int W> __device__ __forceinline__ void unpack_slots(const ElemArgs &a, uint32_t t, uint32_t *s) {
-    if (W == 1) {
+    if (W != 2) {
         const uint32_t w = ldc<uint32_t>(a.slot[0], t);
         s[0] = w & 255u;
         s[1] = (w >> 8) & 255u;
@@ -837,6 +837,7 @@ template <class T, int MODEL, int OP>
 static void launch_block(int tpt, int w, int red, const ElemArgs &a, int threads, unsigned grid, size_t shmem,
                          hipStream_t s) {
     if (w == 1) launch_block_w<T, MODEL, OP, 1>(tpt, red, a, threads, grid, shmem, s);
+    else if (w == 3 && sizeof(T) == 4) launch_block_w<float, MODEL, OP, 3>(tpt, red, a, threads, grid, shmem, s);
     else launch_block_w<T, MODEL, OP, 2>(tpt, red, a, threads, grid, shmem, s);
 }
 
@@ -921,6 +922,17 @@ static ElemArgs base_args(ebbx_fem_s *F) {
     a.own_vb = (uint32_t)F->own_vb;
     a.own_nblk = (uint32_t)F->own_nblk;
     return a;
+}
+
+// The per-tet arrays of the block kernels in the tables' order, where that is not the rows' own.
+static void order_args(const ebbx_fem_s *F, ElemArgs &a) {
+    if (!F->ordered) return;
+    const size_t col = (size_t)F->nt * F->esize;
+    for (int k = 0; k < 9; ++k) a.B[k] = F->B_ord.get() ? (const char *)F->B_ord.get() + k * col : nullptr;
+    if (F->per_tet) {
+        a.mu_t = F->mat_ord.get();
+        a.lam_t = (const char *)F->mat_ord.get() + col;
+    }
 }
 
 static void set_vec(const double *(&dst)[3], const double *p, uint32_t nv) {
@@ -1030,6 +1042,7 @@ void elem_launch(ebbx_fem_s *F, ElemOp op, const double *d, const double *u, dou
         return;
     }
     if (F->strategy == EBBX_STRAT_BLOCK || F->strategy == EBBX_STRAT_BLOCK_LDS || F->strategy == EBBX_STRAT_LANES) {
+        order_args(F, a);
         const size_t shmem = block_shmem(F, op);
         if (shmem > lds_limit())
             fail(EBBX_E_STATE, "block strategy needs %zu bytes of LDS per block (%d vertices); reorder the mesh "
@@ -1269,6 +1282,7 @@ void elem_set_material(ebbx_fem_s *F, const double *E_tet, const double *nu_tet,
     else
         hipLaunchKernelGGL(k_material<double>, dim3(g), dim3(256), 0, s, E_tet, nu_tet, E, nu, F->nt, F->mat.as<double>());
     HIPCHK(hipGetLastError());
+    refresh_ordered(F, s);
 }
 
 // ---- rest-shape precompute -----------------------------------------------------------------
@@ -1396,6 +1410,7 @@ void elem_launch_pre(ebbx_fem_s *F, const double *d, const double *u, double *f,
     for (int ph = 0; ph < 3; ++ph)
         for (int k = 0; k < 3; ++k) a.pre_out[ph][k] = outs[ph] + (size_t)k * nv;
     a.halo9 = F->halo9.as<double>();
+    order_args(F, a);
     const size_t shmem = block_shmem(F, OP_KMUL);   // d and u staged, one row set
     if (shmem > lds_limit())
         fail(EBBX_E_STATE, "block strategy needs %zu bytes of LDS per block (%d vertices); reorder the mesh "
@@ -1407,9 +1422,11 @@ void elem_launch_pre(ebbx_fem_s *F, const double *d, const double *u, double *f,
     if (F->prec == EBBX_F32) {
         if (F->model == EBBX_STVK) {
             if (F->blk_w == 1) go(k_block_pre<float, EBBX_STVK, 1>);
+            else if (F->blk_w == 3) go(k_block_pre<float, EBBX_STVK, 3>);
             else go(k_block_pre<float, EBBX_STVK, 2>);
         } else {
             if (F->blk_w == 1) go(k_block_pre<float, EBBX_NH, 1>);
+            else if (F->blk_w == 3) go(k_block_pre<float, EBBX_NH, 3>);
             else go(k_block_pre<float, EBBX_NH, 2>);
         }
     } else {

@@ -172,8 +172,11 @@ void build_halo(ebbx_fem_s *F, const std::vector<int32_t> &verts, const std::vec
                 const std::vector<int64_t> &rp, std::vector<int32_t> &hpos, hipStream_t s);
 void upload_block_tables(ebbx_fem_s *F, const HostBlocks &hb, const std::vector<int32_t> &hpos, hipStream_t s);
 // Build the tet-block tables of the BLOCK strategies with a halo of the blocks' shared vertices,
-// on the device (tables.hip).
-void build_blocks(ebbx_fem_s *F, int32_t tets_per_block, hipStream_t s);
+// on the device (tables.hip).  reorder: the tables may follow a locality order of the tets
+// (t_order) where the rows' own order has none.
+void build_blocks(ebbx_fem_s *F, int32_t tets_per_block, bool reorder, hipStream_t s);
+// Bring the copies of per-tet arrays in the tables' order up to date (after a change of material).
+void refresh_ordered(ebbx_fem_s *F, hipStream_t s);
 // The block-local FP32 rest positions of the current block tables (FP32 elements on blocks of at
 // most 256 vertices; released otherwise).
 void build_block_xf(ebbx_fem_s *F, hipStream_t s);
@@ -204,7 +207,7 @@ void fem_unregister(ebbx_fem_s *F);
 // Validate and build a FEM domain (synchronous); E_tet: per-tet modulus or NULL.
 std::unique_ptr<ebbx_fem_s> fem_build(ebbx_relation_s *tr, const char *keyfield, ebbx_relation_s *vr,
                                       const char *pos_field, const char *pinned_field, const ebbx_fem_params &p,
-                                      const double *E_tet);
+                                      const double *E_tet, bool may_order);
 // Select the scatter strategy and block size (builds block tables as needed).
 void set_strategy(ebbx_fem_s *F, int32_t strategy, int32_t block, hipStream_t s);
 // Drop the captured solver graphs (solve.hip); they bake in kernel arguments.
@@ -241,7 +244,13 @@ struct ebbx_fem_s {
     int32_t blk_tpt = 1;       // tets per thread (block kernels run blk_tets / blk_tpt threads)
     int64_t nblk = 0;
     int32_t blk_maxv = 0;      // largest vertex count of one block
-    int32_t blk_w = 1;         // 32-bit words of packed corner slots per tet
+    int32_t blk_w = 1;         // corner slots and rest shapes: 1: one 32-bit word of slots per tet, B
+                               // recomputed from the staged rest positions; 2: two words, B streamed;
+                               // 3: one word, B streamed
+    bool may_order = true;     // the tables may follow t_order (not the union of a batch)
+    bool ordered = false;      // they do: row i of the tables is tet t_order[i]
+    bool order_settled = false;   // that choice was made for the present tables
+    ebbx::DevBuf t_order, B_ord, mat_ord;   // the order, and per-tet arrays in it
     int32_t blk_red = 0;       // 0: incidence-list sums (deterministic), 1: FP64 LDS atomics
     int64_t sh_n = 0;          // vertices summed from the halo (shared or untouched)
     int64_t halo_n = 0;        // halo entries

@@ -90,7 +90,10 @@ void set_strategy(ebbx_fem_s *F, int32_t strategy, int32_t block, hipStream_t s)
         if (two && bt < 128) fail(EBBX_E_ARG, "two tets per thread need blocks of at least 128 tets");
         if ((two || bt > 512) && bt % 128)
             fail(EBBX_E_ARG, "two tets per thread need a multiple of 128 tets per block (got %d)", bt);
-        if (!F->blocks_built || F->blk_tets != bt || F->halo_level != 0) build_blocks(F, bt, s);
+        // LANES keeps the rows' own order
+        const bool reorder = F->may_order && strategy != EBBX_STRAT_LANES;
+        if (!F->blocks_built || F->blk_tets != bt || F->halo_level != 0 || (reorder ? !F->order_settled : F->ordered))
+            build_blocks(F, bt, reorder, s);
         F->strategy = strategy;
         F->blk_red = strategy == EBBX_STRAT_BLOCK_LDS ? 1 : 0;
         F->blk_tpt = (two || bt > 512) ? 2 : 1;
@@ -107,7 +110,7 @@ void set_strategy(ebbx_fem_s *F, int32_t strategy, int32_t block, hipStream_t s)
 
 std::unique_ptr<ebbx_fem_s> fem_build(ebbx_relation_s *tr, const char *keyfield, ebbx_relation_s *vr,
                                       const char *pos_field, const char *pinned_field, const ebbx_fem_params &prm,
-                                      const double *E_tet) {
+                                      const double *E_tet, bool may_order) {
     const ebbx_fem_params *params = &prm;
     KeyField &kf = get_key(tr, keyfield);
     if (kf.target != vr) fail(EBBX_E_ARG, "key-field '%s' does not target '%s'", keyfield, vr->name.c_str());
@@ -140,6 +143,7 @@ std::unique_ptr<ebbx_fem_s> fem_build(ebbx_relation_s *tr, const char *keyfield,
     F->lam = params->E * params->nu / ((1.0 + params->nu) * (1.0 - 2.0 * params->nu));
     F->per_tet = E_tet != nullptr;
     F->E_tet = E_tet;
+    F->may_order = may_order;
     F->group = build_group(tr, keyfield, s);
     const int64_t nt = std::max<int64_t>(F->nt, 1), nv = std::max<int64_t>(F->nv, 1);
     F->B.reset((size_t)nt * 9 * F->esize, s);
@@ -179,7 +183,7 @@ ebbx_status ebbx_fem_create(ebbx_relation tets, const char *keyfield, ebbx_relat
     auto *vr = check_rel(verts);
     const double *E_tet = nullptr;
     if (params->E_field) E_tet = (const double *)get_field(tr, params->E_field, EBBX_F64, 1).ptr;
-    auto F = fem_build(tr, keyfield, vr, pos_field, pinned_field, *params, E_tet);
+    auto F = fem_build(tr, keyfield, vr, pos_field, pinned_field, *params, E_tet, true);
     fem_register(F.get());
     *out = F.release();
     EBBX_API_END

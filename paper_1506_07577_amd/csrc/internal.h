@@ -156,6 +156,13 @@ void exclusive_scan_i64(int64_t *data, int64_t n, hipStream_t s);  // in place, 
 void radix_sort_pairs_u32(uint32_t *keys, uint32_t *vals, int64_t n, int bits, hipStream_t s);
 void radix_sort_pairs_u64(uint64_t *keys, uint32_t *vals, int64_t n, int bits, hipStream_t s);
 
+// A locality order of a mesh's tets (new -> old): by the smallest place of their corners in a
+// Morton order (10 bits per axis) of the FP64 (3, nv) positions, ties in the present order.
+// Synchronous.
+void locality_order(const double *X, int64_t nv, const int32_t *keys, int64_t nt, uint32_t *tids, hipStream_t s);
+// dst[c][i] = src[c][perm[i]] for ncomp columns of n entries of 4 or 8 bytes.
+void permute_columns(const void *src, void *dst, size_t esize, const int32_t *perm, int64_t n, int ncomp, hipStream_t s);
+
 int current_device();
 
 // Whether a live domain holds per-row data of relation r in r's present order (a FEM

@@ -465,6 +465,31 @@ __global__ void k_min_key(const int32_t *keys, int64_t n, int arity, const int32
     }
 }
 
+// The bounding box of the positions and the scale to 2^21 steps per axis.  Synchronous.
+static MortonFrame morton_frame(const double *X, int64_t nv, hipStream_t s) {
+    MortonFrame fr;
+    for (int a = 0; a < 3; ++a) { fr.lo[a] = 0.0; fr.sc[a] = 0.0; }
+    if (nv > 0) {
+        const unsigned nb = grid_for(nv, 256, 1024);
+        DevBuf part((size_t)nb * 6 * sizeof(double), s);
+        hipLaunchKernelGGL(k_bbox, dim3(nb), dim3(256), 0, s, X, nv, part.as<double>());
+        HIPCHK(hipGetLastError());
+        std::vector<double> h((size_t)nb * 6);
+        HIPCHK(hipMemcpy(h.data(), part.get(), h.size() * sizeof(double), hipMemcpyDeviceToHost));
+        double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+        for (unsigned b = 0; b < nb; ++b)
+            for (int a = 0; a < 3; ++a) {
+                lo[a] = std::min(lo[a], h[6 * b + a]);
+                hi[a] = std::max(hi[a], h[6 * b + 3 + a]);
+            }
+        for (int a = 0; a < 3; ++a) {
+            fr.lo[a] = lo[a];
+            fr.sc[a] = hi[a] > lo[a] ? 2097152.0 / (hi[a] - lo[a]) : 0.0;
+        }
+    }
+    return fr;
+}
+
 // ---- reorder ---------------------------------------------------------------------------
 
 template <class E>
@@ -475,6 +500,45 @@ __global__ void k_gather_rows(const E *src, E *dst, const int32_t *perm, int64_t
         int64_t c = j / n, i = j - c * n;
         dst[j] = src[c * n + perm[i]];
     }
+}
+
+// The top 30 bits of each Morton code.
+__global__ void k_code_top(const uint64_t *codes, int64_t n, uint32_t *out) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        out[i] = (uint32_t)(codes[i] >> 33);
+}
+
+void locality_order(const double *X, int64_t nv, const int32_t *keys, int64_t nt, uint32_t *tids, hipStream_t s) {
+    if (nv == 0 || nt == 0) return;
+    const MortonFrame fr = morton_frame(X, nv, s);
+    DevBuf codes((size_t)nv * sizeof(uint64_t), s), top((size_t)nv * sizeof(uint32_t), s);
+    DevBuf vids((size_t)nv * sizeof(uint32_t), s), inv((size_t)nv * sizeof(int32_t), s), tk((size_t)nt * sizeof(uint32_t), s);
+    hipLaunchKernelGGL(k_morton_codes, dim3(grid_for(nv, 256, 16384)), dim3(256), 0, s, X, nv, fr,
+                       codes.as<uint64_t>(), vids.as<uint32_t>());
+    HIPCHK(hipGetLastError());
+    hipLaunchKernelGGL(k_code_top, dim3(grid_for(nv, 256, 16384)), dim3(256), 0, s, codes.as<uint64_t>(), nv,
+                       top.as<uint32_t>());
+    HIPCHK(hipGetLastError());
+    radix_sort_pairs_u32(top.as<uint32_t>(), vids.as<uint32_t>(), nv, 30, s);
+    hipLaunchKernelGGL(k_invert, dim3(grid_for(nv, 256, 16384)), dim3(256), 0, s, vids.as<uint32_t>(), nv,
+                       inv.as<int32_t>());
+    HIPCHK(hipGetLastError());
+    hipLaunchKernelGGL(k_min_key, dim3(grid_for(nt, 256, 16384)), dim3(256), 0, s, keys, nt, 4, inv.as<int32_t>(),
+                       tk.as<uint32_t>(), tids);
+    HIPCHK(hipGetLastError());
+    radix_sort_pairs_u32(tk.as<uint32_t>(), tids, nt, bits_for(nv), s);
+}
+
+void permute_columns(const void *src, void *dst, size_t esize, const int32_t *perm, int64_t n, int ncomp, hipStream_t s) {
+    if (n == 0) return;
+    const dim3 g(grid_for(n * ncomp, 256, 65536));
+    if (esize == 4)
+        hipLaunchKernelGGL(k_gather_rows<uint32_t>, g, dim3(256), 0, s, (const uint32_t *)src, (uint32_t *)dst, perm, n,
+                           ncomp);
+    else
+        hipLaunchKernelGGL(k_gather_rows<uint64_t>, g, dim3(256), 0, s, (const uint64_t *)src, (uint64_t *)dst, perm, n,
+                           ncomp);
+    HIPCHK(hipGetLastError());
 }
 
 __global__ void k_remap_keys(int32_t *keys, int64_t total, const int32_t *inv) {
@@ -661,27 +725,7 @@ ebbx_status ebbx_morton_order(ebbx_relation verts, const char *pos_field, const 
     }
     const int64_t nv = vr->size, nt = tr->size;
     hipStream_t s = nullptr;
-    // bounding box
-    MortonFrame fr;
-    for (int a = 0; a < 3; ++a) { fr.lo[a] = 0.0; fr.sc[a] = 0.0; }
-    if (nv > 0) {
-        const unsigned nb = grid_for(nv, 256, 1024);
-        DevBuf part((size_t)nb * 6 * sizeof(double), s);
-        hipLaunchKernelGGL(k_bbox, dim3(nb), dim3(256), 0, s, (const double *)X.ptr, nv, part.as<double>());
-        HIPCHK(hipGetLastError());
-        std::vector<double> h((size_t)nb * 6);
-        HIPCHK(hipMemcpy(h.data(), part.get(), h.size() * sizeof(double), hipMemcpyDeviceToHost));
-        double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-        for (unsigned b = 0; b < nb; ++b)
-            for (int a = 0; a < 3; ++a) {
-                lo[a] = std::min(lo[a], h[6 * b + a]);
-                hi[a] = std::max(hi[a], h[6 * b + 3 + a]);
-            }
-        for (int a = 0; a < 3; ++a) {
-            fr.lo[a] = lo[a];
-            fr.sc[a] = hi[a] > lo[a] ? 2097152.0 / (hi[a] - lo[a]) : 0.0;
-        }
-    }
+    const MortonFrame fr = morton_frame((const double *)X.ptr, nv, s);
     DevBuf codes((size_t)std::max<int64_t>(nv, 1) * sizeof(uint64_t), s);
     DevBuf vids((size_t)std::max<int64_t>(nv, 1) * sizeof(uint32_t), s);
     if (nv > 0) {

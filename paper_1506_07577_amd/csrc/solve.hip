@@ -1450,7 +1450,7 @@ ebbx_status ebbx_batch_create(ebbx_relation meshes, ebbx_relation tets, ebbx_rel
     ebbx_fem_params up = *params;
     up.E = 1.0;
     up.nu = 0.25;
-    B->fem = fem_build(tr, fields->tet_verts, vr, fields->pos, fields->pinned, up, nullptr);
+    B->fem = fem_build(tr, fields->tet_verts, vr, fields->pos, fields->pinned, up, nullptr, false);
     ebbx_fem_s *F = B->fem.get();
     const int64_t nt = F->nt, nv = F->nv;
     // layout: verts and tets sorted by mesh, every tet inside its mesh

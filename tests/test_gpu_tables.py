@@ -60,3 +60,45 @@ def test_block_tables(name, bt):
     mesh.fem.forces(mesh.to_dev(d))
     mesh.fem.set_strategy(ebbx.STRAT_BLOCK, bt)
     assert torch.equal(f, mesh.fem.forces(mesh.to_dev(d)))
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("model", [0, 1])
+def test_tables_in_a_locality_order(model, prec):
+    """A scrambled mesh, whose rows' order has no locality: the tables follow an order of their own,
+    and so must everything per tet that the block kernels read (rest shapes, a material that
+    changes), through changes of strategy.  Normwise 1e-10 (FP64) and 1e-5 (FP32 elements)."""
+    m, _, _ = mg.scramble(mg.jitter(mg.kuhn_cube(11), 0.01, seed=0), seed=1)
+    bound = 1e-10 if prec == "f64" else 1e-5
+    rng = np.random.default_rng(3)
+    E = [1e5 * np.exp(0.5 * rng.standard_normal(m.nt)) for _ in range(2)]
+    d, u, w = mg.perturbed_state(m, 0.02, seed=10), mg.direction(m, 11), mg.direction(m, 12)
+    mesh = ebbx.FemMesh(m.X, m.tets, m.pinned, model=model, elem_prec=ebbx.F64 if prec == "f64" else ebbx.F32,
+                        E=1e5, nu=0.3, strategy=ebbx.STRAT_BLOCK)
+    fem, dd, du, dw = mesh.fem, *(mesh.to_dev(a) for a in (d, u, w))
+
+    def check(ref):
+        err = lambda got, want: np.abs(mesh.from_dev(got) - want).max() / np.abs(want).max()
+        assert err(fem.forces(dd), ref.forces(d)) <= bound
+        assert err(fem.kmul(dd, du), ref.kmul(d, u)) <= bound
+        assert err(fem.tmul(dd, du, dw), ref.tmul(d, u, w)) <= bound
+        assert err(fem.jacobi_diag(dd, 1e-3), ref.jacobi_diag(d, 1e-3)) <= bound
+        x, v = mesh.to_dev(d), mesh.to_dev(0.01 * u)
+        st = fem.implicit_step(x, v, 1e-3, maxit=12)
+        assert ebbx.stats_fetch(st).status == 0
+        _d1, v1, _dv, _s = ref.implicit_step(d, 0.01 * u, 1e-3, maxit=12)
+        assert err(v, v1) <= 10 * bound
+
+    check(oracle.FEM.create(model, m.X, m.tets, 1e5, 0.3, pinned=m.pinned))
+    for Et, how in zip(E, ((ebbx.STRAT_LANES, 128), (ebbx.STRAT_SEG, 0))):
+        fem.set_material(E_tet=mesh.tet_to_dev(Et), nu=0.3)
+        ref = oracle.FEM.create(model, m.X, m.tets, Et, 0.3, pinned=m.pinned)
+        check(ref)
+        fem.set_strategy(*how)
+        check(ref)
+        fem.set_strategy(ebbx.STRAT_BLOCK, 256)
+        check(ref)
+        fem.set_strategy(ebbx.STRAT_BLOCK_LDS, 128)
+        check(ref)
+        fem.set_strategy(ebbx.STRAT_BLOCK, 512 | ebbx.BLOCK_TPT2)
+        check(ref)
