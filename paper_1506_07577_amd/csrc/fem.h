@@ -111,6 +111,9 @@ struct ElemArgs {
 void elem_launch(ebbx_fem_s *F, ElemOp op, const double *d, const double *u, double *out, int accumulate,
                  hipStream_t s, const int *skip = nullptr, const double *w = nullptr, const int *mdone = nullptr,
                  bool finish_halo = true, void *scratch = nullptr, const int32_t *act = nullptr);
+// The arguments of a BLOCK-strategy kernel of map `op` (its shared vertices left in the domain's
+// halo), and the dynamic LDS it needs; fails if a workgroup cannot hold it.
+ElemArgs elem_block_args(ebbx_fem_s *F, ElemOp op, const double *d, const double *u, double *out, size_t *shmem);
 // Whether the element map `op` of F's strategy can run over an active list (act of
 // elem_launch, batches only): the stiffness product of the BLOCK strategy, one tet per thread.
 bool elem_list_ok(const ebbx_fem_s *F, ElemOp op);
@@ -257,6 +260,7 @@ struct ebbx_fem_s {
     ebbx::DevBuf blk_xf;   // block-local FP32 rest positions (FP32 elements, blocks of <= 256 vertices)
     ebbx::DevBuf blk_verts, blk_lptr, blk_pos, blk_hpos, blk_local, halo, sh_vert, sh_ptr, sh_pos, sh_tab,
         sh_row;
+    ebbx::DevBuf pair_tab;     // per-vertex halo places of the two-kernel CG iterations
     ebbx::DevBuf halo9;        // the fused step preamble's halo (9 values per entry)
     int32_t sh_nc = 0;         // int4 chunks per row of sh_tab (0: use the CSR form)
     bool blocks_built = false;

@@ -23,26 +23,9 @@
 #include <mutex>
 #include <set>
 
-#include "fem.h"
+#include "pair.h"
 
 namespace ebbx {
-
-// CG state of one mesh, kept on the device.
-struct CGState {
-    double rz, rr, pq, alpha, beta, bnorm;
-    int iters, status, done, converged;
-    unsigned long long n_inv;
-};
-
-// Solve-wide flags: meshes still iterating; all_done = 1 once none is.  The
-// per-mesh finished flags (nm ints) follow the struct in memory.
-struct SolveCtl {
-    int n_active, all_done;
-};
-
-__device__ __forceinline__ int *mesh_done(SolveCtl *c) { return (int *)(c + 1); }
-
-constexpr int VT = 256;   // threads of the vertex kernels = vertices per chunk
 
 // Chunks of the vertex range: chunk c covers vertices [lo[c], hi[c]) of mesh
 // mesh[c]; the chunks of mesh m are [cptr[m], cptr[m+1]).
@@ -80,119 +63,6 @@ __device__ __forceinline__ ChunkAt chunk_at(const Chunks &ch, int64_t nv) {
 static unsigned grid_one(int nch, int cpw) { return (unsigned)((nch + cpw - 1) / cpw); }
 
 static unsigned grid_for(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (n + VT - 1) / VT)); }
-
-// Sum of one double over a 256-thread block (fixed order).
-__device__ __forceinline__ double block_sum(double x, double *s4) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) s4[threadIdx.x >> 6] = x;
-    __syncthreads();
-    return (s4[0] + s4[1]) + (s4[2] + s4[3]);
-}
-
-// N block sums at once (s: 4 N doubles), each combined exactly as block_sum combines one.
-template <int N>
-__device__ __forceinline__ void block_sums(double (&x)[N], double *s) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-        for (int i = 0; i < N; ++i) x[i] += __shfl_xor(x[i], o, 64);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0)
-#pragma unroll
-        for (int i = 0; i < N; ++i) s[4 * i + (threadIdx.x >> 6)] = x[i];
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < N; ++i) x[i] = (s[4 * i] + s[4 * i + 1]) + (s[4 * i + 2] + s[4 * i + 3]);
-}
-
-// Chunk partials, 4 doubles per chunk: [0] p.q, [1] r.r, [2 + parity] r.z of the
-// iterations of that parity (the initial residual counts as parity 1).
-constexpr int PQ = 0, RR = 1, RZ = 2;
-
-// Each thread's share of a fixed-order sum over chunks [c0, c1): acc[s] += the partials at
-// offset o[s] of chunks c0 + t, c0 + t + VT, c0 + t + 2 VT, ... in that order.  The loads of
-// PART_BATCH strided chunks are issued before any of them is added, so a workgroup waits for
-// one round trip per batch rather than one per chunk; the order of the additions is unchanged.
-constexpr int PART_BATCH = 8;
-template <int NS>
-__device__ __forceinline__ void part_acc(const double *part, int c0, int c1, const int (&o)[NS], double (&acc)[NS]) {
-    for (int cb = c0 + (int)threadIdx.x; cb < c1; cb += PART_BATCH * VT) {
-        double l[PART_BATCH][NS];
-#pragma unroll
-        for (int j = 0; j < PART_BATCH; ++j) {
-            const int c = cb + j * VT;
-#pragma unroll
-            for (int s = 0; s < NS; ++s) l[j][s] = c < c1 ? part[4 * c + o[s]] : 0.0;
-        }
-#pragma unroll
-        for (int j = 0; j < PART_BATCH; ++j)
-            if (cb + j * VT < c1)
-#pragma unroll
-                for (int s = 0; s < NS; ++s) acc[s] += l[j][s];
-    }
-}
-
-// Fixed-order sum of the partials at offset o of chunks [c0, c1).
-__device__ __forceinline__ double sum_parts(const double *part, int c0, int c1, int o, double *s4) {
-    double acc[1] = {0.0};
-    part_acc<1>(part, c0, c1, {o}, acc);
-    return block_sum(acc[0], s4);
-}
-
-// Three fixed-order sums at once (offsets o0, o1, o2), each with exactly the
-// operation order of sum_parts, sharing the barriers.
-__device__ __forceinline__ void sum_parts3(const double *part, int c0, int c1, int o0, int o1, int o2, double *s12,
-                                           double &r0, double &r1, double &r2) {
-    double acc[3] = {0.0, 0.0, 0.0};
-    part_acc<3>(part, c0, c1, {o0, o1, o2}, acc);
-    double a0 = acc[0], a1 = acc[1], a2 = acc[2];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        a0 += __shfl_xor(a0, o, 64);
-        a1 += __shfl_xor(a1, o, 64);
-        a2 += __shfl_xor(a2, o, 64);
-    }
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
-        s12[threadIdx.x >> 6] = a0;
-        s12[4 + (threadIdx.x >> 6)] = a1;
-        s12[8 + (threadIdx.x >> 6)] = a2;
-    }
-    __syncthreads();
-    r0 = (s12[0] + s12[1]) + (s12[2] + s12[3]);
-    r1 = (s12[4] + s12[5]) + (s12[6] + s12[7]);
-    r2 = (s12[8] + s12[9]) + (s12[10] + s12[11]);
-}
-
-// Two fixed-order sums at once (offsets o0, o1), as sum_parts3.
-__device__ __forceinline__ void sum_parts2(const double *part, int c0, int c1, int o0, int o1, double *s12, double &r0,
-                                           double &r1) {
-    double acc[2] = {0.0, 0.0};
-    part_acc<2>(part, c0, c1, {o0, o1}, acc);
-    double a0 = acc[0], a1 = acc[1];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        a0 += __shfl_xor(a0, o, 64);
-        a1 += __shfl_xor(a1, o, 64);
-    }
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
-        s12[threadIdx.x >> 6] = a0;
-        s12[4 + (threadIdx.x >> 6)] = a1;
-    }
-    __syncthreads();
-    r0 = (s12[0] + s12[1]) + (s12[2] + s12[3]);
-    r1 = (s12[4] + s12[5]) + (s12[6] + s12[7]);
-}
-
-// One thread of the mesh's block marks mesh m finished.
-__device__ __forceinline__ void mark_done(CGState &st, SolveCtl *ctl, int m) {
-    st.done = 1;
-    mesh_done(ctl)[m] = 1;
-    if (atomicSub(&ctl->n_active, 1) == 1) ctl->all_done = 1;
-}
 
 // Rebuild the active list (ActList) of a batched solve from the meshes' finished flags, at the
 // start of a CG iteration; one workgroup.  Mesh m's tets are [tptr[m], tptr[m+1]), its blocks
@@ -251,10 +121,6 @@ __global__ __launch_bounds__(VT) void k_active(const SolveCtl *ctl, const int64_
         hdr[3] = 0;
     }
 }
-
-struct StepVec {
-    double *dn, *vn, *f, *y, *r, *z, *p, *q, *x, *diag;
-};
 
 __global__ void k_step_begin(CGState *st, int nm, SolveCtl *ctl, unsigned long long *n_inv) {
     for (int m = blockIdx.x * blockDim.x + threadIdx.x; m < nm; m += gridDim.x * blockDim.x) {
@@ -375,42 +241,6 @@ __global__ __launch_bounds__(VT) void k_step_init(CGState *st, const double *par
             mark_done(s, ctl, m);
         }
     }
-}
-
-// Vertex v's value of an element-map output that may still have its shared
-// vertices' sums in the halo (same summation order as the halo pass).
-__device__ __forceinline__ void finished(const HaloView &h, const double *y, int64_t nv, int64_t v, double *o) {
-    const int32_t r = h.row ? h.row[v] : -1;
-    if (r < 0) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) o[k] = y[k * nv + v];
-        return;
-    }
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-    if (h.nc > 0) {
-        for (int c = 0; c < h.nc; ++c) {
-            const int4 q = h.tab[(size_t)r * h.nc + c];
-            const int32_t p4[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (p4[k] >= 0) {
-                    const double *hq = h.halo + 3 * (size_t)p4[k];
-                    a0 += hq[0];
-                    a1 += hq[1];
-                    a2 += hq[2];
-                }
-        }
-    } else {
-        for (int32_t j = h.ptr[r]; j < h.ptr[r + 1]; ++j) {
-            const double *hq = h.halo + 3 * (size_t)h.pos[j];
-            a0 += hq[0];
-            a1 += hq[1];
-            a2 += hq[2];
-        }
-    }
-    o[0] = a0;
-    o[1] = a1;
-    o[2] = a2;
 }
 
 // q = Pi (cm M p - ck y); chunk partial p.q (y finished here if the element map left it in the halo)
@@ -795,7 +625,8 @@ __global__ __launch_bounds__(VT) void k_cg_p_one(StepVec w, int64_t nv, int nch,
 
 // One CG iteration after K p for a single mesh of at most SMALL_NV vertices, in one workgroup:
 // the passes of k_cg_Ap, k_cg_update_f and k_cg_p_f with workgroup barriers where the large
-// solve needs a launch (each dot product is one fixed-order workgroup sum).  The CG scalars live
+// solve needs a launch (each dot product is one fixed-order workgroup sum), for the strategies
+// and block sizes whose iterations do not run in two kernels (pair.hip).  The CG scalars live
 // in the mesh's state (r.z carried there from one iteration to the next).  A small mesh's
 // iteration is launch-bound, so two launches instead of four halve it.
 constexpr int SMALL_T = 1024;
@@ -991,6 +822,7 @@ using namespace ebbx;
 
 struct ebbx_fem_s::Step {
     DevBuf vec, part, state, ctl, chunks;
+    DevBuf part_k;        // block partials of the two-kernel iterations (pair.hip)
     DevBuf act, tptr;   // batches: the active list and the meshes' tet offsets (nm + 1)
     StepVec w{};
     Chunks ch{};
@@ -1056,6 +888,7 @@ struct SolveBufs {
     double *part;
     int nch, nm;
     bool fused;
+    double *part_k;         // block partials of the two-kernel iterations
     int32_t *act;           // batches: the active list (NULL: every kernel covers every mesh)
     const int64_t *tptr;    // batches: the meshes' tet offsets
 };
@@ -1094,10 +927,15 @@ void launch_preamble(ebbx_fem_s *F, const ebbx_step_params &p, int mode, const S
 }
 
 // `count` CG iterations (at most maxit) onto stream cs, starting at an even iteration (the
-// fused kernels pick r.z slots by iteration parity).  Every kernel is predicated on its
+// fused kernels pick r.z slots by iteration parity); first: at the solve's first one.  Every kernel is predicated on its
 // mesh's done flag, the element map on the solve-wide all_done flag.
-void launch_iterations(ebbx_fem_s *F, const ebbx_step_params &p, const SolveBufs &b, int count, hipStream_t cs) {
+void launch_iterations(ebbx_fem_s *F, const ebbx_step_params &p, const SolveBufs &b, int count, bool first,
+                       hipStream_t cs) {
     const int64_t nv = F->nv;
+    if (b.fused && pair_ok(F)) {
+        pair_iterations(F, p, b.w, b.st, b.ctl, b.part, b.part_k, b.nch, count, first, cs);
+        return;
+    }
     // K p: a block-strategy element map leaves its shared vertices in the halo and
     // k_cg_Ap finishes them as it reads y (one launch and one y round trip fewer)
     const HaloView hv = elem_halo_view(F);
@@ -1165,7 +1003,7 @@ void launch_iterations(ebbx_fem_s *F, const ebbx_step_params &p, const SolveBufs
 SolveBufs step_bufs(ebbx_fem_s *F) {
     auto &S = *F->step;
     return SolveBufs{S.w, S.ch, S.state.as<CGState>(), S.ctl.as<SolveCtl>(), S.part.as<double>(), S.nch, S.nm,
-                     S.fused, S.nm > 1 ? S.act.as<int32_t>() : nullptr,
+                     S.fused, S.part_k.as<double>(), S.nm > 1 ? S.act.as<int32_t>() : nullptr,
                      S.nm > 1 ? S.tptr.as<int64_t>() : nullptr};
 }
 
@@ -1178,6 +1016,11 @@ void build_graphs(ebbx_fem_s *F, const ebbx_step_params &p, int mode) {
                       S.precond == p.precond && S.strategy == F->strategy && S.block == F->block && S.valid;
     if (!same) S.drop_graphs();
     if (S.pre[mode]) return;
+    // the two-kernel iterations' block partials and halo places, allocated outside the capture
+    if (pair_ok(F) && !S.valid) {
+        S.part_k.reset((size_t)F->nblk * sizeof(double), S.cap);
+        pair_prepare(F, S.cap);
+    }
     const SolveBufs b = step_bufs(F);
     hipStream_t cs = S.cap;
     if (pre_fused(F, p, mode)) elem_pre_prepare(F, cs);   // its halo, allocated outside the capture
@@ -1196,13 +1039,13 @@ void build_graphs(ebbx_fem_s *F, const ebbx_step_params &p, int mode) {
         fail(EBBX_E_STATE, "CG chunk sizes must be even");
     // the preamble graph also holds the first chunk, so a solve that converges
     // within it is one graph launch
-    launch_iterations(F, p, b, S.first_iters, cs);
+    launch_iterations(F, p, b, S.first_iters, true, cs);
     guard.disarm();
     S.pre[mode] = capture_end(cs, &S.g_pre[mode]);
     if (!S.chunk && p.maxit > S.first_iters) {
         capture_begin(cs);
         CaptureGuard chunk_guard(cs);
-        launch_iterations(F, p, b, S.chunk_iters, cs);
+        launch_iterations(F, p, b, S.chunk_iters, false, cs);
         chunk_guard.disarm();
         S.chunk = capture_end(cs, &S.g_chunk);
     }

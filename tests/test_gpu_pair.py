@@ -1,0 +1,103 @@
+"""CG iterations in two kernels (a single mesh under the BLOCK strategy, up to 2048 blocks of 256 tets)
+against the oracle at the edges: one block and one vertex chunk, ragged last ones, a vertex shared by
+more blocks than the fixed-width halo rows hold, vertices with no tet, odd iteration counts, solves
+stopped inside, at the end of and past the first captured chunk, and by a breakdown.
+
+Tolerances (normwise): 1e-10 (FP64) and 1e-5 (FP32 elements) for fixed iteration counts, 1e-9 for
+FP64 solves stopped by a tolerance of 1e-11 or below."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1506_07577_amd import meshgen as mg
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from paper_1506_07577_amd import ebbx
+else:  # collected on a CPU host only to be deselected
+    ebbx = None
+
+
+def _hub(cells):
+    """Jittered cells of six tets that all share one corner (vertex 1); vertex 0 and the last one
+    have no tet and are pinned."""
+    cell = mg.kuhn_cube(1)
+    rng = np.random.default_rng(7)
+    X = np.concatenate([np.ones((1, 3)), np.zeros((1, 3))]
+                       + [cell.X[1:] + 0.01 * rng.uniform(-1.0, 1.0, size=(7, 3)) for _ in range(cells)]
+                       + [np.ones((1, 3))])
+    tets = [np.where(cell.tets == 0, 1, cell.tets + 1 + 7 * c) for c in range(cells)]
+    pinned = np.zeros(len(X), dtype=np.uint8)
+    pinned[2:5] = 1
+    pinned[[0, -1]] = 1   # a free vertex needs a mass
+    return mg.Mesh(X=X, tets=np.concatenate(tets).astype(np.int32), pinned=pinned, n=0, h=0.3)
+
+
+MESHES = {
+    "one_tet": lambda: mg.single_tet(),
+    "one_chunk": lambda: mg.jitter(mg.kuhn_cube(5), 0.01, seed=0),     # 216 vertices, 750 tets
+    "odd": lambda: mg.jitter(mg.kuhn_cube(13), 0.01, seed=0),          # 2744 vertices, 11 chunks
+    "scrambled": lambda: mg.scramble(mg.jitter(mg.kuhn_cube(9), 0.01, seed=0), seed=1)[0],
+    "hub": lambda: _hub(800),                                          # its vertex in 19 blocks
+}
+
+
+def _both(m, model, prec, maxit, tol, damped=False, **kw):
+    mesh = ebbx.FemMesh(m.X, m.tets, m.pinned, model=model, elem_prec=ebbx.F64 if prec == "f64" else ebbx.F32,
+                        E=1e5, nu=0.3, strategy=ebbx.STRAT_BLOCK, morton=kw.get("morton", False))
+    ref = oracle.FEM.create(model, m.X, m.tets, 1e5, 0.3, pinned=m.pinned)
+    alpha, beta = (2.5, 4e-3) if damped else (0.0, 0.0)
+    d0, v0 = mg.perturbed_state(m, 0.02, seed=10), 0.05 * mg.direction(m, 11)
+    d, v = mesh.to_dev(d0), mesh.to_dev(v0)
+    out = []
+    for _ in range(2):   # the second step replays the captured graphs
+        st = ebbx.stats_fetch(mesh.fem.implicit_step(d, v, 1e-3, tol=tol, maxit=maxit, alpha=alpha, beta=beta))
+        d0, v0, _dv, so = ref.implicit_step(d0, v0, 1e-3, tol=tol, maxit=maxit, alpha=alpha, beta=beta)
+        assert (st.iters, st.status) == (so.iters, so.status)
+        out.append(np.abs(mesh.from_dev(v) - v0).max() / np.abs(v0).max())
+    return max(out)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("model", [0, 1])
+@pytest.mark.parametrize("name", sorted(MESHES))
+def test_fixed_count(name, model, prec):
+    bound = 1e-10 if prec == "f64" else 1e-5
+    for maxit in (1, 2, 7):
+        assert _both(MESHES[name](), model, prec, maxit, 0.0, damped=maxit == 7) <= bound
+
+
+@pytest.mark.parametrize("tol", [1e-3, 1e-11, 1e-14])
+def test_to_a_tolerance(tol):
+    m = mg.jitter(mg.kuhn_cube(13), 0.01, seed=0)
+    mesh = ebbx.FemMesh(m.X, m.tets, m.pinned, model=ebbx.NH, elem_prec=ebbx.F64, E=1e6, nu=0.45,
+                        strategy=ebbx.STRAT_BLOCK, morton=True)
+    ref = oracle.FEM.create(ebbx.NH, m.X, m.tets, 1e6, 0.45, pinned=m.pinned)
+    d0, v0 = mg.perturbed_state(m, 0.02, seed=10), 0.05 * mg.direction(m, 11)
+    d, v = mesh.to_dev(d0), mesh.to_dev(v0)
+    st = ebbx.stats_fetch(mesh.fem.implicit_step(d, v, 1e-3, tol=tol, maxit=500))
+    _d1, v1, _dv, so = ref.implicit_step(d0, v0, 1e-3, tol=tol, maxit=500)
+    assert st.status == so.status == ebbx.OK and abs(st.iters - so.iters) <= 1
+    assert st.rel_res <= tol
+    if tol <= 1e-11:
+        assert np.abs(mesh.from_dev(v) - v1).max() <= 1e-9 * np.abs(v1).max()
+
+
+def test_not_converged_and_breakdown():
+    m = mg.jitter(mg.kuhn_cube(6), 0.01, seed=0)
+    for maxit in (3, 32, 41):   # inside, at the end of and past the first chunk of a tolerance solve
+        mesh = ebbx.FemMesh(m.X, m.tets, m.pinned, model=ebbx.STVK, elem_prec=ebbx.F64, E=1e5, nu=0.3,
+                            strategy=ebbx.STRAT_BLOCK)
+        d, v = mesh.to_dev(mg.perturbed_state(m, 0.02, seed=10)), mesh.to_dev(0.05 * mg.direction(m, 11))
+        st = ebbx.stats_fetch(mesh.fem.implicit_step(d, v, 1e-3, tol=1e-300, maxit=maxit))
+        assert (st.iters, st.status) == (maxit, ebbx.E_NOT_CONVERGED)
+    # a negative modulus makes A indefinite for a large enough dt: the state stays as it was
+    mesh = ebbx.FemMesh(m.X, m.tets, m.pinned, model=ebbx.STVK, elem_prec=ebbx.F64, E=-1e9, nu=0.3,
+                        strategy=ebbx.STRAT_BLOCK)
+    d, v = mesh.to_dev(mg.perturbed_state(m, 0.02, seed=10)), mesh.to_dev(0.05 * mg.direction(m, 11))
+    d0, v0 = d.clone(), v.clone()
+    st = ebbx.stats_fetch(mesh.fem.implicit_step(d, v, 1e-2, maxit=50, precond=ebbx.PRECOND_NONE))
+    assert st.status == ebbx.E_NOT_SPD
+    assert torch.equal(d, d0) and torch.equal(v, v0)
