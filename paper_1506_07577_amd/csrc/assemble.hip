@@ -23,6 +23,7 @@
 
 #include "fem.h"
 #include "tetmath.h"
+#include "wave.h"
 
 namespace ebbx {
 
@@ -407,12 +408,9 @@ __global__ __launch_bounds__(256) void k_bsr_spmv(BsrArgs<T> a) {
         y1 += (double)a.k[3][e] * u0 + (double)a.k[4][e] * u1 + (double)a.k[5][e] * u2;
         y2 += (double)a.k[6][e] * u0 + (double)a.k[7][e] * u1 + (double)a.k[8][e] * u2;
     }
-#pragma unroll
-    for (int m = SPMV_LANES / 2; m >= 1; m >>= 1) {
-        y0 += __shfl_xor(y0, m, SPMV_LANES);
-        y1 += __shfl_xor(y1, m, SPMV_LANES);
-        y2 += __shfl_xor(y2, m, SPMV_LANES);
-    }
+    y0 = lanes_sum<SPMV_LANES>(y0);
+    y1 = lanes_sum<SPMV_LANES>(y1);
+    y2 = lanes_sum<SPMV_LANES>(y2);
     if (lane == 0 && g < a.nv) {
         if (a.accumulate) {
             y0 += a.y[0][i];

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "fem.h"
+#include "wave.h"
 
 namespace ebbx {
 
@@ -25,8 +26,7 @@ constexpr int VT = 256;   // threads of the vertex kernels = vertices per chunk
 
 // Sum of one double over a 256-thread block (fixed order).
 __device__ __forceinline__ double block_sum(double x, double *s4) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    x = lanes_sum<64>(x);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) s4[threadIdx.x >> 6] = x;
     __syncthreads();
@@ -37,9 +37,7 @@ __device__ __forceinline__ double block_sum(double x, double *s4) {
 template <int N>
 __device__ __forceinline__ void block_sums(double (&x)[N], double *s) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-        for (int i = 0; i < N; ++i) x[i] += __shfl_xor(x[i], o, 64);
+    for (int i = 0; i < N; ++i) x[i] = lanes_sum<64>(x[i]);
     __syncthreads();
     if ((threadIdx.x & 63) == 0)
 #pragma unroll
@@ -89,13 +87,7 @@ __device__ __forceinline__ void sum_parts3(const double *part, int c0, int c1, i
                                            double &r0, double &r1, double &r2) {
     double acc[3] = {0.0, 0.0, 0.0};
     part_acc<3>(part, c0, c1, {o0, o1, o2}, acc);
-    double a0 = acc[0], a1 = acc[1], a2 = acc[2];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        a0 += __shfl_xor(a0, o, 64);
-        a1 += __shfl_xor(a1, o, 64);
-        a2 += __shfl_xor(a2, o, 64);
-    }
+    const double a0 = lanes_sum<64>(acc[0]), a1 = lanes_sum<64>(acc[1]), a2 = lanes_sum<64>(acc[2]);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {
         s12[threadIdx.x >> 6] = a0;
@@ -113,12 +105,7 @@ __device__ __forceinline__ void sum_parts2(const double *part, int c0, int c1, i
                                            double &r1) {
     double acc[2] = {0.0, 0.0};
     part_acc<2>(part, c0, c1, {o0, o1}, acc);
-    double a0 = acc[0], a1 = acc[1];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        a0 += __shfl_xor(a0, o, 64);
-        a1 += __shfl_xor(a1, o, 64);
-    }
+    const double a0 = lanes_sum<64>(acc[0]), a1 = lanes_sum<64>(acc[1]);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {
         s12[threadIdx.x >> 6] = a0;

@@ -633,8 +633,7 @@ constexpr int SMALL_T = 1024;
 constexpr int64_t SMALL_NV = 4096;
 
 __device__ __forceinline__ double block_sum_small(double x, double *s16) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    x = lanes_sum<64>(x);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) s16[threadIdx.x >> 6] = x;
     __syncthreads();

@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "fem.h"
+#include "wave.h"
 
 struct ebbx_springs_s {
     const ebbx_relation_s *edges = nullptr, *verts = nullptr;   // the relations the row copies follow
@@ -133,12 +134,9 @@ __device__ __forceinline__ void spring_sum(const int32_t *head, const double *re
             f2 += fma(-sc, c[u], c[u]);
         }
     }
-#pragma unroll
-    for (int m = L / 2; m >= 1; m >>= 1) {
-        f0 += __shfl_xor(f0, m, L);
-        f1 += __shfl_xor(f1, m, L);
-        f2 += __shfl_xor(f2, m, L);
-    }
+    f0 = lanes_sum<L>(f0);
+    f1 = lanes_sum<L>(f1);
+    f2 = lanes_sum<L>(f2);
 }
 
 // The exclusive update of one vertex component: a = f / m, q += qd dt + a dt^2 / 2, qd += a dt.
@@ -208,8 +206,7 @@ __global__ void k_spring_apply(const double *mass, double dt, double *q, double 
 }
 
 __device__ __forceinline__ double block_total(double x, double *s4) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    x = lanes_sum<64>(x);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) s4[threadIdx.x >> 6] = x;
     __syncthreads();
