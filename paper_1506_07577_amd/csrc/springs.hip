@@ -5,9 +5,11 @@
 //  - rest lengths: one pass over the edges (the example's per-edge kernel);
 //  - forces: each vertex loops over the edges leaving it (the grouping of the
 //    edges by their tail key-field) and reduces (+=) the spring forces into its
-//    force field: four lanes per vertex, each lane a stride of the vertex's
-//    edges with two edges' loads in flight, the row sum a fixed butterfly over
-//    the four lanes, one division per edge and K applied to the sum;
+//    force field, one division per edge and K applied to the sum.  Where
+//    neighbouring vertices share neighbours, a workgroup stages the positions
+//    that its 128 vertices need in LDS once (k_spring_block); elsewhere four
+//    lanes per vertex gather them from memory, two edges' loads in flight per
+//    lane (k_spring_forces, k_spring_step);
 //  - apply: the exclusive per-vertex update (integrate, clear the force);
 //  - kinetic energy: a global += as a fixed-order two-pass sum;
 //  - run: nsteps replayed from a captured HIP graph of 32 steps, each step one
@@ -33,6 +35,11 @@ struct ebbx_springs_s {
     ebbx::DevBuf rest;   // FP64 (ne): rest length of each edge, in row order
     ebbx::DevBuf part;   // FP64 partials of the energy sum
     ebbx::DevBuf q2;     // FP64 (3 nv): the other position buffer of the fused steps of a run
+    // k_spring_block (stride 0: not used), `lanes` lanes per vertex: per workgroup the sorted list of
+    // the vertices it reads (-1 padded to the stride) and the place of its own first one; per wave
+    // its edges, padded to the same number per lane, lane-major
+    int32_t stride = 0, lanes = 2;
+    ebbx::DevBuf b_list, b_own, b_off, b_slot, b_rest;
     // captured steps of ebbx_springs_run
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
@@ -96,6 +103,32 @@ __global__ void k_spring_setup(const int64_t *rp, const int32_t *inc, const int3
         const double a = X[h] - x0, b = X[nv + h] - x1, c = X[2 * nv + h] - x2;
         rest[p] = sqrt(a * a + b * b + c * c);
     }
+}
+
+// len / sqrt(n2), 0 for n2 = 0 (a zero-length spring pulls with K dq), where n2 is 0 or in
+// [1e-280, 1e280].  One hardware reciprocal square root (about 2^-24) serves the root and the
+// quotient: two coupled Newton steps give the root and half its reciprocal, a residual step
+// corrects the root, another the quotient.  No branch, so that the loads of the edges after it can
+// be issued before it.  Bit for bit the library's len / sqrt(n2) on 4M random arguments each in
+// [0.5, 1.5] x [0.25, 3.25], over 9 and 17 decades and over 260 and 555 decades.
+__device__ __forceinline__ double spring_scale(double len, double n2) {
+    const double y = __builtin_amdgcn_rsq(n2);
+    double g = n2 * y, h = 0.5 * y;   // -> sqrt(n2), 1 / (2 sqrt(n2))
+    double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    r = fma(-h, g, 0.5);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, n2), h, g);
+    const double q = len * (2.0 * h);
+    const double s = fma(fma(-g, q, len), 2.0 * h, q);
+    return n2 == 0.0 ? 0.0 : s;
+}
+__device__ __forceinline__ bool spring_in_range(double n2) { return n2 == 0.0 || (n2 >= 1e-280 && n2 <= 1e280); }
+// The same for any n2 (and NaN).
+__device__ __forceinline__ double spring_scale_any(double len, double n2) {
+    const double n = sqrt(n2);
+    return n > 0.0 ? len / n : 0.0;
 }
 
 // Sum over the edges leaving vertex v ([e0, e1) of the rows) of dq - L dq/|dq|, dq = q_h - q_v
@@ -193,6 +226,305 @@ __global__ __launch_bounds__(256) void k_spring_step(const int32_t *row, const i
     }
 }
 
+// ---- positions staged in LDS -------------------------------------------------------------------
+
+constexpr int SB_T = 256;                  // threads of a workgroup: 256 / L vertices, L lanes each
+constexpr int SB_U = 2;                    // edges of a lane in flight together
+// Lanes per vertex: four on meshes too small to fill the chip with two (8^3 cells 4.6 us per step
+// with two, 3.8 with four; 32^3 5.7 and 5.0; 48^3, 118k vertices, 8.5 and 9.4).
+constexpr int64_t SB_FOUR_NV = 65536;
+constexpr int SB_MAX = 4096;               // edges and vertices of one workgroup (table construction)
+constexpr int SB_STRIDE = 1024;            // staged vertices of one workgroup (24 KiB of LDS)
+
+struct SpringBlocks {
+    const int32_t *list, *own;   // [nwg * stride], [nwg]
+    const int64_t *off;          // [4 nwg + 1]: first entry of each wave, 64 per edge round
+    const uint16_t *slot;        // head's place in the workgroup's list
+    const double *rest;
+    uint32_t stride, nv;
+};
+
+// The distinct vertices that workgroup wg's vertices and edges touch, sorted into s[0, *nu); false
+// if there are more than SB_MAX of them with repeats.
+__device__ __forceinline__ bool spring_list(const int32_t *row, const int32_t *head, int64_t v0, int64_t v1,
+                                            uint32_t *s, int32_t *s_n, int32_t *nu) {
+    const int64_t e0 = row[v0], ne = row[v1] - e0, own = v1 - v0;
+    if (ne + own > SB_MAX) return false;
+    const int32_t m = (int32_t)(ne + own);
+    int32_t n = 256;
+    while (n < m) n <<= 1;
+    for (int32_t i = threadIdx.x; i < n; i += SB_T)
+        s[i] = i < ne ? (uint32_t)head[e0 + i] : i < m ? (uint32_t)(v0 + i - ne) : ~0u;
+    __syncthreads();
+    for (int32_t k = 2; k <= n; k <<= 1)
+        for (int32_t j = k >> 1; j > 0; j >>= 1) {
+            for (int32_t e = threadIdx.x; e < n / 2; e += SB_T) {
+                const int32_t i = ((e & ~(j - 1)) << 1) | (e & (j - 1)), o = i | j;
+                const uint32_t x = s[i], y = s[o];
+                if ((x > y) == ((i & k) == 0)) {
+                    s[i] = y;
+                    s[o] = x;
+                }
+            }
+            __syncthreads();
+        }
+    // compact in place: every thread reads its stretch before any writes
+    const int32_t per = n / SB_T, i0 = (int32_t)threadIdx.x * per;
+    uint32_t keep[SB_MAX / SB_T];
+    int32_t cnt = 0;
+#pragma unroll
+    for (int32_t u = 0; u < SB_MAX / SB_T; ++u) {
+        const int32_t i = i0 + u;
+        keep[u] = ~0u;
+        if (u < per && s[i] != ~0u && (i == 0 || s[i] != s[i - 1])) {
+            keep[u] = s[i];
+            ++cnt;
+        }
+    }
+    s_n[threadIdx.x] = cnt;
+    __syncthreads();
+    int32_t at = 0, total = 0;
+    for (int32_t w = 0; w < SB_T; ++w) {
+        if (w < (int32_t)threadIdx.x) at += s_n[w];
+        total += s_n[w];
+    }
+#pragma unroll
+    for (int32_t u = 0; u < SB_MAX / SB_T; ++u)
+        if (keep[u] != ~0u) s[at++] = keep[u];
+    __syncthreads();
+    *nu = total;
+    return true;
+}
+
+// got[0]: the most vertices that a workgroup stages (2^30 if one has too many edges); off[4 wg + w]:
+// entries of wave w (its longest vertex's rounds, 64 entries each); *staged: all lists together.
+template <int L>
+__global__ __launch_bounds__(SB_T) void k_spring_count(const int32_t *row, const int32_t *head, int64_t nv, int *most,
+                                                       unsigned long long *staged, int64_t *off) {
+    __shared__ uint32_t s[SB_MAX];
+    __shared__ int32_t s_n[SB_T], s_deg[4];
+    constexpr int V = SB_T / L, W = 64 / L;   // vertices per workgroup and per wave
+    const int64_t v0 = (int64_t)blockIdx.x * V, v1 = v0 + V < nv ? v0 + V : nv;
+    if (threadIdx.x < 4) s_deg[threadIdx.x] = 0;
+    int32_t nu = 0;
+    const bool fits = spring_list(row, head, v0, v1, s, s_n, &nu);   // uniform over the workgroup
+    __syncthreads();
+    const int64_t v = v0 + threadIdx.x;
+    if (threadIdx.x < V && v < v1) atomicMax(&s_deg[threadIdx.x / W], row[v + 1] - row[v]);
+    __syncthreads();
+    if (threadIdx.x < 4)
+        off[4 * (int64_t)blockIdx.x + threadIdx.x] = fits ? (int64_t)((s_deg[threadIdx.x] + L - 1) / L) * 64 : 0;
+    if (threadIdx.x == 0) {
+        atomicMax(most, fits ? nu : 1 << 30);
+        atomicAdd(staged, (unsigned long long)nu);
+    }
+}
+
+template <int L>
+__global__ __launch_bounds__(SB_T) void k_spring_fill(const int32_t *row, const int32_t *head, const double *rest,
+                                                      int64_t nv, int32_t stride, const int64_t *off, int32_t *list,
+                                                      int32_t *own, uint16_t *slot, double *brest) {
+    __shared__ uint32_t s[SB_MAX];
+    __shared__ int32_t s_n[SB_T];
+    constexpr int V = SB_T / L;
+    const int64_t wg = blockIdx.x, v0 = wg * V, v1 = v0 + V < nv ? v0 + V : nv;
+    int32_t nu = 0;
+    if (!spring_list(row, head, v0, v1, s, s_n, &nu)) return;
+    auto place = [&](uint32_t v) {
+        int32_t lo = 0, hi = nu - 1;
+        while (lo < hi) {
+            const int32_t mid = (lo + hi) >> 1;
+            if (s[mid] < v) lo = mid + 1;
+            else hi = mid;
+        }
+        return lo;
+    };
+    for (int32_t i = threadIdx.x; i < stride; i += SB_T) list[wg * stride + i] = i < nu ? (int32_t)s[i] : -1;
+    const int32_t first = place((uint32_t)v0);
+    if (threadIdx.x == 0) own[wg] = first;
+    const int32_t lv = (int32_t)threadIdx.x / L, sub = (int32_t)threadIdx.x % L;
+    const int64_t v = v0 + lv, w = 4 * wg + threadIdx.x / 64;
+    const int32_t e0 = v < nv ? row[v] : 0, e1 = v < nv ? row[v + 1] : 0;
+    int32_t e = e0 + sub;
+    for (int64_t j = off[w] + threadIdx.x % 64; j < off[w + 1]; j += 64, e += L) {
+        // a padding entry is a spring from the lane's vertex to itself: no force
+        slot[j] = (uint16_t)(e < e1 ? place((uint32_t)head[e]) : v < nv ? first + lv : 0);
+        brest[j] = e < e1 ? rest[e] : 0.0;
+    }
+}
+
+// Forces (STEP 0) or one whole step (STEP 1; see k_spring_step) of a workgroup's 256 / L vertices, L
+// lanes each.  The positions come into LDS once per workgroup (about 3 per vertex on a
+// Morton-ordered tet mesh, against 14 gathers), the edges lane-major, 10 bytes each and coalesced.
+// Bound by memory: 60 MB read and 14 MB written per step at 64^3 cells (275k vertices, 3.74M edges),
+// 15.5 us or 4.8 TB/s, the rate of a large copy; k_spring_step, bound by its gathers, 21.3 us.
+// Measured: one / two / four / eight edges in flight 17.1 / 15.5 / 16.4 / 18.2 us; with the
+// library's square root and division 16.3; the rest lengths recomputed from staged rest positions
+// in place of read, 18.1; 256 vertices on 512 threads no faster.
+template <int STEP, int L>
+__global__ __launch_bounds__(SB_T) void k_spring_block(SpringBlocks t, double K, const double *mass, double dt,
+                                                       const double *q, double *q_out, double *qd, double *f,
+                                                       int take_f) {
+    extern __shared__ double s_q[];
+    const uint32_t tid = threadIdx.x, S = t.stride, nv = t.nv;
+    const uint32_t wg = xcd_block(blockIdx.x, gridDim.x);
+    const uint32_t lv = tid / L, v = wg * (SB_T / L) + lv;
+    const bool in = v < nv;
+    const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / 64));
+    const int64_t w0 = t.off[4 * (int64_t)wg + wv], j0 = w0 + (tid & 63u);
+    const int32_t rounds = (int32_t)((t.off[4 * (int64_t)wg + wv + 1] - w0) / 64);
+    const uint32_t me = (uint32_t)t.own[wg] + (in ? lv : 0u);
+    // what the update reads, in flight while the positions are staged: lane `sub` of a vertex takes
+    // the components sub, sub + L
+    constexpr int NC = L >= 3 ? 1 : 2;
+    const uint32_t sub = tid % L;
+    double m = 1.0, vel[NC], f0[NC];
+    if (in) {
+        if (STEP) m = mass[v];
+#pragma unroll
+        for (int i = 0; i < NC; ++i)
+            if (sub + i * L < 3) {
+                const size_t at = (size_t)(sub + i * L) * nv + v;
+                if (STEP) vel[i] = qd[at];
+                if (take_f) f0[i] = f[at];
+            }
+    }
+    for (uint32_t i = tid; i < S; i += SB_T) {
+        const int32_t g = t.list[(size_t)wg * S + i];
+        if (g >= 0)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) s_q[k * S + i] = q[(size_t)k * nv + g];
+    }
+    // the edges, SB_U rounds at a time, the next ones in flight while these are summed (every lane
+    // of a wave has the same number of rounds)
+    uint32_t h[SB_U];
+    double len[SB_U];
+    auto load = [&](int32_t r) {
+#pragma unroll
+        for (int u = 0; u < SB_U; ++u) {
+            const bool on = r + u < rounds;
+            h[u] = on ? t.slot[j0 + (int64_t)(r + u) * 64] : me;
+            len[u] = on ? t.rest[j0 + (int64_t)(r + u) * 64] : 0.0;
+        }
+    };
+    load(0);
+    __syncthreads();
+    const double q0 = s_q[me], q1 = s_q[S + me], q2 = s_q[2 * S + me];
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+    bool fine = true;
+    for (int32_t r = 0; r < rounds; r += SB_U) {
+        double a[SB_U], b[SB_U], c[SB_U], l[SB_U];
+#pragma unroll
+        for (int u = 0; u < SB_U; ++u) {
+            a[u] = s_q[h[u]] - q0;
+            b[u] = s_q[S + h[u]] - q1;
+            c[u] = s_q[2 * S + h[u]] - q2;
+            l[u] = len[u];
+        }
+        load(r + SB_U);
+#pragma unroll
+        for (int u = 0; u < SB_U; ++u) {
+            const double n2 = a[u] * a[u] + b[u] * b[u] + c[u] * c[u];
+            const double sc = spring_scale(l[u], n2);
+            fine = fine && spring_in_range(n2);
+            a0 += fma(-sc, a[u], a[u]);
+            a1 += fma(-sc, b[u], b[u]);
+            a2 += fma(-sc, c[u], c[u]);
+        }
+    }
+    if (!fine) {   // a spring of extreme or no finite length: this lane's sum again
+        a0 = a1 = a2 = 0.0;
+        for (int32_t r = 0; r < rounds; ++r) {
+            const uint32_t k = t.slot[j0 + (int64_t)r * 64];
+            const double x = s_q[k] - q0, y = s_q[S + k] - q1, z = s_q[2 * S + k] - q2;
+            const double sc = spring_scale_any(t.rest[j0 + (int64_t)r * 64], x * x + y * y + z * z);
+            a0 += fma(-sc, x, x);
+            a1 += fma(-sc, y, y);
+            a2 += fma(-sc, z, z);
+        }
+    }
+    a0 = lanes_sum<L>(a0);
+    a1 = lanes_sum<L>(a1);
+    a2 = lanes_sum<L>(a2);
+    if (!in) return;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        const uint32_t c = sub + i * L;
+        if (c >= 3) break;
+        const size_t at = (size_t)c * nv + v;
+        double fk = K * (c == 0 ? a0 : c == 1 ? a1 : a2);
+        if (take_f) fk += f0[i];
+        if (STEP) {
+            if (take_f) f[at] = 0.0;
+            double qn, vn;
+            integrate(c == 0 ? q0 : c == 1 ? q1 : q2, vel[i], fk / m, dt, qn, vn);
+            q_out[at] = qn;
+            qd[at] = vn;
+        } else {
+            f[at] = fk;
+        }
+    }
+}
+
+SpringBlocks spring_blocks(const ebbx_springs_s *S) {
+    return SpringBlocks{S->b_list.as<int32_t>(), S->b_own.as<int32_t>(), S->b_off.as<int64_t>(),
+                        S->b_slot.as<uint16_t>(), S->b_rest.as<double>(), (uint32_t)S->stride, (uint32_t)S->nv};
+}
+
+// The tables of k_spring_block, where they pay: the workgroups' lists together hold at most half as
+// many vertices as there are edges (else staging saves little), each few enough for six workgroups'
+// LDS per CU, and padding the waves to their longest vertex adds at most half (else a few vertices
+// of high degree make every lane of their wave wait).  Synchronous.
+template <int L> void build_spring_blocks(ebbx_springs_s *S, hipStream_t s) {
+    const int64_t nv = S->nv, ne = S->ne;
+    if (nv == 0 || ne == 0) return;
+    const int64_t nwg = (nv + SB_T / L - 1) / (SB_T / L);
+    DevBuf got(16, s);
+    S->b_off.reset((size_t)(4 * nwg + 1) * sizeof(int64_t), s);
+    HIPCHK(hipMemsetAsync(got.get(), 0, 16, s));
+    HIPCHK(hipMemsetAsync(S->b_off.get(), 0, S->b_off.bytes(), s));
+    hipLaunchKernelGGL(k_spring_count<L>, dim3((unsigned)nwg), dim3(SB_T), 0, s, S->row.as<int32_t>(),
+                       S->head.as<int32_t>(), nv, got.as<int>(), got.as<unsigned long long>() + 1,
+                       S->b_off.as<int64_t>());
+    HIPCHK(hipGetLastError());
+    exclusive_scan_i64(S->b_off.as<int64_t>(), 4 * nwg + 1, s);
+    int64_t h[2] = {0, 0}, entries = 0;
+    HIPCHK(hipMemcpyAsync(h, got.get(), sizeof h, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(&entries, S->b_off.as<int64_t>() + 4 * nwg, sizeof entries, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    const int32_t most = (int32_t)(h[0] & 0x7fffffff);
+    if (most > SB_STRIDE || 2 * h[1] > ne || 2 * entries > 3 * ne) {
+        S->b_off.release();
+        return;
+    }
+    S->b_list.reset((size_t)nwg * most * sizeof(int32_t), s);
+    S->b_own.reset((size_t)nwg * sizeof(int32_t), s);
+    S->b_slot.reset((size_t)entries * sizeof(uint16_t), s);
+    S->b_rest.reset((size_t)entries * sizeof(double), s);
+    hipLaunchKernelGGL(k_spring_fill<L>, dim3((unsigned)nwg), dim3(SB_T), 0, s, S->row.as<int32_t>(),
+                       S->head.as<int32_t>(), S->rest.as<double>(), nv, most, S->b_off.as<int64_t>(),
+                       S->b_list.as<int32_t>(), S->b_own.as<int32_t>(), S->b_slot.as<uint16_t>(),
+                       S->b_rest.as<double>());
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(s));
+    S->stride = most;
+    S->lanes = L;
+}
+
+template <int STEP>
+void launch_block(ebbx_springs_s *S, const double *mass, double dt, const double *q, double *q_out, double *qd,
+                  double *f, int take_f, hipStream_t s) {
+    const dim3 g(blocks_of(S->nv * S->lanes, SB_T));
+    const size_t lds = (size_t)3 * S->stride * sizeof(double);
+    if (S->lanes == 4)
+        hipLaunchKernelGGL((k_spring_block<STEP, 4>), g, dim3(SB_T), lds, s, spring_blocks(S), S->K, mass, dt, q,
+                           q_out, qd, f, take_f);
+    else
+        hipLaunchKernelGGL((k_spring_block<STEP, 2>), g, dim3(SB_T), lds, s, spring_blocks(S), S->K, mass, dt, q,
+                           q_out, qd, f, take_f);
+    HIPCHK(hipGetLastError());
+}
+
 __global__ void k_spring_apply(const double *mass, double dt, double *q, double *qd, double *f, int64_t nv) {
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += (int64_t)gridDim.x * blockDim.x) {
         const double m = mass[v];
@@ -237,6 +569,10 @@ __global__ __launch_bounds__(EN_THREADS) void k_kinetic_sum(const double *part, 
 
 void launch_forces(ebbx_springs_s *S, const double *q, double *f, int accumulate, hipStream_t s) {
     if (S->nv == 0) return;
+    if (S->stride) {
+        launch_block<0>(S, nullptr, 0.0, q, nullptr, nullptr, f, accumulate, s);
+        return;
+    }
     hipLaunchKernelGGL((k_spring_forces<LANES, UNROLL>), dim3(blocks_of(S->nv * LANES, 256)), dim3(256), 0, s,
                        S->row.as<int32_t>(), S->head.as<int32_t>(), S->rest.as<double>(), S->K, q, f,
                        (uint32_t)S->nv, accumulate);
@@ -245,6 +581,10 @@ void launch_forces(ebbx_springs_s *S, const double *q, double *f, int accumulate
 
 void launch_step(ebbx_springs_s *S, const double *mass, double dt, const double *q, double *q_out, double *qd,
                  double *f, int take_f, hipStream_t s) {
+    if (S->stride) {
+        launch_block<1>(S, mass, dt, q, q_out, qd, f, take_f, s);
+        return;
+    }
     hipLaunchKernelGGL((k_spring_step<LANES, UNROLL>), dim3(blocks_of(S->nv * LANES, 256)), dim3(256), 0, s,
                        S->row.as<int32_t>(), S->head.as<int32_t>(), S->rest.as<double>(), S->K, mass, dt, q, q_out,
                        qd, f, take_f, (uint32_t)S->nv);
@@ -313,6 +653,8 @@ extern "C" ebbx_status ebbx_springs_create(ebbx_relation edges, const char *tail
                        g->row_ptr.as<int64_t>(), g->inc.as<int32_t>(), kh.ptr, (const double *)X.ptr, S->nv,
                        S->row.as<int32_t>(), S->head.as<int32_t>(), S->rest.as<double>());
     HIPCHK(hipGetLastError());
+    if (S->nv <= SB_FOUR_NV) build_spring_blocks<4>(S.get(), nullptr);
+    else build_spring_blocks<2>(S.get(), nullptr);
     HIPCHK(hipStreamCreateWithFlags(&S->cap, hipStreamNonBlocking));
     HIPCHK(hipDeviceSynchronize());
     {
