@@ -14,10 +14,13 @@ struct CGState {
     unsigned long long n_inv;
 };
 
-// Solve-wide flags: meshes still iterating; all_done = 1 once none is.  The
-// per-mesh finished flags (nm ints) follow the struct in memory.
+// Solve-wide flags: meshes still iterating; all_done = 1 once none is, when the solve's number is
+// also written to *host (pinned host memory), for a host that waits on the solve.  The per-mesh
+// finished flags (nm ints) follow the struct in memory.
 struct SolveCtl {
     int n_active, all_done;
+    int solve, pad;
+    int *host;
 };
 
 __device__ __forceinline__ int *mesh_done(SolveCtl *c) { return (int *)(c + 1); }
@@ -120,7 +123,10 @@ __device__ __forceinline__ void sum_parts2(const double *part, int c0, int c1, i
 __device__ __forceinline__ void mark_done(CGState &st, SolveCtl *ctl, int m) {
     st.done = 1;
     mesh_done(ctl)[m] = 1;
-    if (atomicSub(&ctl->n_active, 1) == 1) ctl->all_done = 1;
+    if (atomicSub(&ctl->n_active, 1) == 1) {
+        ctl->all_done = 1;
+        __hip_atomic_store(ctl->host, ctl->solve, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 struct StepVec {

@@ -724,7 +724,10 @@ __global__ __launch_bounds__(SMALL_T) void k_cg_iter_small(StepVec w, const doub
         }
 }
 
-__global__ void k_copy_in(const double *d, const double *v, double *dn, double *vn, int64_t n) {
+// solve: this solve's number, which its end reports to the host
+__global__ void k_copy_in(const double *d, const double *v, double *dn, double *vn, int64_t n, SolveCtl *ctl,
+                          int solve) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->solve = solve;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         dn[i] = d[i];
         vn[i] = v[i];
@@ -759,7 +762,9 @@ __global__ __launch_bounds__(VT) void k_step_end(StepVec w, int64_t nv, double d
 }
 
 // adjoint: d_n copied in, g^ = gv + dt gx into f (the solve's right-hand side)
-__global__ void k_vjp_prep(const double *d, const double *gx, const double *gv, double dt, StepVec w, int64_t n) {
+__global__ void k_vjp_prep(const double *d, const double *gx, const double *gv, double dt, StepVec w, int64_t n,
+                           SolveCtl *ctl, int solve) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->solve = solve;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         w.dn[i] = d[i];
         w.f[i] = gv[i] + dt * gx[i];
@@ -836,7 +841,11 @@ struct ebbx_fem_s::Step {
     // parameters baked into the graphs
     double dt = -1, g[3] = {0, 0, 0}, tol = -1, alpha = -1, beta = -1;
     int maxit = -1, precond = -1, strategy = -1, block = -1;
-    int *h_done = nullptr;   // pinned host flag for convergence checks
+    // convergence checks: the number of the present solve, and the number of the last one that
+    // ended, written by the device (pinned host memory)
+    int solve = 0;
+    int *h_done = nullptr;
+    hipEvent_t ev = nullptr;   // the end of the last graph launched
     void drop_graphs() {
         for (int k = 0; k < 2; ++k) {
             if (pre[k]) (void)hipGraphExecDestroy(pre[k]);
@@ -853,7 +862,11 @@ struct ebbx_fem_s::Step {
     ~Step() {
         drop_graphs();
         if (cap) (void)hipStreamDestroy(cap);
-        if (h_done) (void)hipHostFree(h_done);
+        if (ev) (void)hipEventDestroy(ev);
+        if (h_done) {
+            (void)hipDeviceSynchronize();   // a solve's last kernels may still report
+            (void)hipHostFree(h_done);
+        }
     }
 };
 
@@ -1119,25 +1132,43 @@ void ensure_step(ebbx_fem_s *F, hipStream_t s) {
     S->state.reset((size_t)std::max<int64_t>(nm, 1) * sizeof(CGState), s);
     S->ctl.reset(sizeof(SolveCtl) + (size_t)std::max<int64_t>(nm, 1) * sizeof(int), s);
     HIPCHK(hipStreamCreateWithFlags(&S->cap, hipStreamNonBlocking));
-    HIPCHK(hipHostMalloc((void **)&S->h_done, sizeof(int), hipHostMallocDefault));
+    HIPCHK(hipHostMalloc((void **)&S->h_done, sizeof(int), hipHostMallocMapped | hipHostMallocCoherent));
+    *S->h_done = 0;
+    SolveCtl c0{};
+    HIPCHK(hipHostGetDevicePointer((void **)&c0.host, S->h_done, 0));
+    HIPCHK(hipMemcpyAsync(S->ctl.get(), &c0, sizeof c0, hipMemcpyHostToDevice, s));
+    HIPCHK(hipEventCreateWithFlags(&S->ev, hipEventDisableTiming));
     HIPCHK(hipStreamSynchronize(s));
     F->step = std::move(S);
+}
+
+// Whether the present solve has ended, once that is known: at the device's report, which comes while
+// the chunk's remaining kernels still return one by one, so that what the host does next is ready
+// when they have; or at the end of the graph launched last, without a report.
+bool solve_ended(ebbx_fem_s::Step &S, hipStream_t s) {
+    HIPCHK(hipEventRecord(S.ev, s));
+    const volatile int *h = S.h_done;
+    for (;;) {
+        if (*h == S.solve) return true;
+        const hipError_t e = hipEventQuery(S.ev);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();
+            continue;
+        }
+        HIPCHK(e);
+        return *h == S.solve;
+    }
 }
 
 // Launch the preamble of `mode` and the CG chunks on s.
 void run_solve(ebbx_fem_s *F, const ebbx_step_params &p, int mode, hipStream_t s) {
     build_graphs(F, p, mode);
     auto &S = *F->step;
-    // preamble + first chunk, then further chunks until maxit
+    // preamble + first chunk, then further chunks until maxit; with a tolerance only until every
+    // mesh has finished
     HIPCHK(hipGraphLaunch(S.pre[mode], s));
-    SolveCtl *ctl = S.ctl.as<SolveCtl>();
     for (int done = S.first_iters; done < p.maxit; done += S.chunk_iters) {
-        // with a tolerance, stop launching once every mesh has finished
-        if (p.tol > 0.0) {
-            HIPCHK(hipMemcpyAsync(S.h_done, &ctl->all_done, sizeof(int), hipMemcpyDeviceToHost, s));
-            HIPCHK(hipStreamSynchronize(s));
-            if (*S.h_done) break;
-        }
+        if (p.tol > 0.0 && solve_ended(S, s)) break;
         HIPCHK(hipGraphLaunch(S.chunk, s));
     }
 }
@@ -1152,11 +1183,9 @@ void implicit_step(ebbx_fem_s *F, double *d, double *v, const ebbx_step_params *
     if (nv > 0 && overlap(d, v, (size_t)(3 * nv) * sizeof(double))) fail(EBBX_E_PHASE, "d aliases v");
     ensure_step(F, s);
     auto &S = *F->step;
-    if (nv > 0) {
-        hipLaunchKernelGGL(k_copy_in, dim3(grid_for(3 * nv)), dim3(VT), 0, s, (const double *)d, (const double *)v,
-                           S.w.dn, S.w.vn, 3 * nv);
-        HIPCHK(hipGetLastError());
-    }
+    hipLaunchKernelGGL(k_copy_in, dim3(grid_for(3 * nv)), dim3(VT), 0, s, (const double *)d, (const double *)v, S.w.dn,
+                       S.w.vn, 3 * nv, S.ctl.as<SolveCtl>(), ++S.solve);
+    HIPCHK(hipGetLastError());
     run_solve(F, p, 0, s);
     hipLaunchKernelGGL(k_step_end, dim3(S.nch), dim3(VT), 0, s, S.w, nv, p.dt, p.tol,
                        (const CGState *)S.state.as<CGState>(), S.ch, d, v, stats);
@@ -1197,10 +1226,9 @@ extern "C" ebbx_status ebbx_implicit_step_vjp(ebbx_fem fem, const double *d_n, c
     hipStream_t s = (hipStream_t)stream;
     ensure_step(F, s);
     auto &S = *F->step;
-    if (nv > 0) {
-        hipLaunchKernelGGL(k_vjp_prep, dim3(grid_for(3 * nv)), dim3(VT), 0, s, d_n, gx, gv, p.dt, S.w, 3 * nv);
-        HIPCHK(hipGetLastError());
-    }
+    hipLaunchKernelGGL(k_vjp_prep, dim3(grid_for(3 * nv)), dim3(VT), 0, s, d_n, gx, gv, p.dt, S.w, 3 * nv,
+                       S.ctl.as<SolveCtl>(), ++S.solve);
+    HIPCHK(hipGetLastError());
     // A w = Pi (gv + dt gx), with A = (1 + dt alpha) M - (dt^2 + dt beta) K(d_n); w ends in x
     run_solve(F, p, 1, s);
     elem_launch(F, OP_KMUL, S.w.dn, S.w.x, S.w.y, 0, s);
