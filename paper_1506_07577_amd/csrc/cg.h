@@ -142,31 +142,21 @@ __device__ __forceinline__ void finished(const HaloView &h, const double *y, int
         for (int k = 0; k < 3; ++k) o[k] = y[k * nv + v];
         return;
     }
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+    double a[3] = {0.0, 0.0, 0.0};
     if (h.nc > 0) {
-        for (int c = 0; c < h.nc; ++c) {
-            const int4 q = h.tab[(size_t)r * h.nc + c];
-            const int32_t p4[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (p4[k] >= 0) {
-                    const double *hq = h.halo + 3 * (size_t)p4[k];
-                    a0 += hq[0];
-                    a1 += hq[1];
-                    a2 += hq[2];
-                }
-        }
+        int n;
+        const int4 *t = h.at(r, n);
+        for (int c = 0; c < n; ++c) halo_add(h.halo, t[c], a);
     } else {
         for (int32_t j = h.ptr[r]; j < h.ptr[r + 1]; ++j) {
             const double *hq = h.halo + 3 * (size_t)h.pos[j];
-            a0 += hq[0];
-            a1 += hq[1];
-            a2 += hq[2];
+            a[0] += hq[0];
+            a[1] += hq[1];
+            a[2] += hq[2];
         }
     }
-    o[0] = a0;
-    o[1] = a1;
-    o[2] = a2;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) o[k] = a[k];
 }
 
 }  // namespace ebbx

@@ -657,42 +657,45 @@ __global__ __launch_bounds__(256) void k_halo_reduce(const double *halo, const i
     }
 }
 
-// The same sum with each shared vertex's halo positions in one fixed-width row
-// (NC x 4 entries, -1 padded, in block order): one dependent load fewer.
+// One shared vertex's sum over its row of NC int4 halo positions (-1 padded, in block order).
 template <int NC>
-__global__ __launch_bounds__(256) void k_halo_tab(const double *halo, const int32_t *sh_vert, const int4 *tab,
-                                                  uint32_t S, double *o0, double *o1, double *o2, int accumulate,
-                                                  const int *skip) {
+__device__ __forceinline__ void halo_row(const double *halo, const int4 *tab, uint32_t v, double *o0, double *o1,
+                                         double *o2, int accumulate) {
+    int4 q[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) q[c] = tab[c];
+    double a[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < NC; ++c) halo_add4(halo, q[c], a);
+    if (accumulate) {
+        a[0] += ldc<double>(o0, v);
+        a[1] += ldc<double>(o1, v);
+        a[2] += ldc<double>(o2, v);
+    }
+    stc<double>(o0, v, a[0]);
+    stc<double>(o1, v, a[1]);
+    stc<double>(o2, v, a[2]);
+}
+
+// The same sum with each shared vertex's halo positions in one fixed-width row: one dependent load
+// fewer.  The first n4 rows hold at most 4 positions (92% of them at 64^3 cells), the others up to
+// 4 NC; workgroups [0, g4) take the former.  With rows of 4 NC for every vertex the pass read
+// padding for a third of its bytes and met up to 12 conditional loads in a row: force + K u at 64^3
+// (FP32) 63.9 us with those, 63.3 with rows of two widths, 61.0 with each int4's entries loaded
+// together as well; 5.2M tets (FP64) 241.6 -> 237.4 us.
+template <int NC>
+__global__ __launch_bounds__(64) void k_halo_tab(const double *halo, const int32_t *sh_vert, const int4 *tab,
+                                                 uint32_t n4, uint32_t S, uint32_t g4, double *o0, double *o1,
+                                                 double *o2, int accumulate, const int *skip) {
     if (skip && *skip) return;
-    // XCD x sums one contiguous eighth of the shared vertices (sorted by id), those of its own
-    // eighth of the Morton-ordered blocks, whose halo entries that XCD wrote
-    const uint32_t wg = xcd_block(blockIdx.x, gridDim.x);
-    for (uint32_t s = wg * blockDim.x + threadIdx.x; s < S; s += gridDim.x * blockDim.x) {
-        const uint32_t v = (uint32_t)sh_vert[s];
-        int4 q[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) q[c] = tab[(size_t)s * NC + c];
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const int32_t p[4] = {q[c].x, q[c].y, q[c].z, q[c].w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (p[k] >= 0) {
-                    const double *hq = halo + 3 * (size_t)p[k];
-                    a0 += hq[0];
-                    a1 += hq[1];
-                    a2 += hq[2];
-                }
-        }
-        if (accumulate) {
-            a0 += ldc<double>(o0, v);
-            a1 += ldc<double>(o1, v);
-            a2 += ldc<double>(o2, v);
-        }
-        stc<double>(o0, v, a0);
-        stc<double>(o1, v, a1);
-        stc<double>(o2, v, a2);
+    // XCD x sums one contiguous eighth of each part (sorted by vertex), the vertices of its own
+    // eighth of the Morton-ordered blocks, whose halo entries that XCD wrote (g4 is a multiple of 8)
+    if (blockIdx.x < g4) {
+        const uint32_t s = xcd_block(blockIdx.x, g4) * 64u + threadIdx.x;
+        if (s < n4) halo_row<1>(halo, tab + s, (uint32_t)sh_vert[s], o0, o1, o2, accumulate);
+    } else {
+        const uint32_t s = n4 + xcd_block(blockIdx.x - g4, gridDim.x - g4) * 64u + threadIdx.x;
+        if (s < S) halo_row<NC>(halo, tab + n4 + (size_t)(s - n4) * NC, (uint32_t)sh_vert[s], o0, o1, o2, accumulate);
     }
 }
 
@@ -898,18 +901,23 @@ static void launch_halo(ebbx_fem_s *F, const double *hl, double *out, int accumu
     // smaller workgroups measured 0.5 us faster than 256-thread ones (more of them in flight
     // per CU, dealt to the XCDs more finely)
     const unsigned T = 64;
-    const dim3 g(grid_n(F->sh_n, T, 1ll << 20));
     const int32_t *sv = F->sh_vert.as<int32_t>();
     const int4 *tb = F->sh_tab.as<int4>();
-    const uint32_t sn = (uint32_t)F->sh_n;
+    const uint32_t sn = (uint32_t)F->sh_n, n4 = (uint32_t)F->sh_n4;
+    const unsigned g4 = ((n4 + T - 1) / T + 7) & ~7u;
+    const dim3 g(g4 + (sn - n4 + T - 1) / T);
+    auto rows = [&](auto kern) {
+        hipLaunchKernelGGL(kern, g, dim3(T), 0, s, hl, sv, tb, n4, sn, g4, out, out + nv, out + 2 * nv, accumulate, skip);
+    };
     switch (F->sh_nc) {
-    case 1: hipLaunchKernelGGL(k_halo_tab<1>, g, dim3(T), 0, s, hl, sv, tb, sn, out, out + nv, out + 2 * nv, accumulate, skip); break;
-    case 2: hipLaunchKernelGGL(k_halo_tab<2>, g, dim3(T), 0, s, hl, sv, tb, sn, out, out + nv, out + 2 * nv, accumulate, skip); break;
-    case 3: hipLaunchKernelGGL(k_halo_tab<3>, g, dim3(T), 0, s, hl, sv, tb, sn, out, out + nv, out + 2 * nv, accumulate, skip); break;
-    case 4: hipLaunchKernelGGL(k_halo_tab<4>, g, dim3(T), 0, s, hl, sv, tb, sn, out, out + nv, out + 2 * nv, accumulate, skip); break;
+    case 1: rows(k_halo_tab<1>); break;
+    case 2: rows(k_halo_tab<2>); break;
+    case 3: rows(k_halo_tab<3>); break;
+    case 4: rows(k_halo_tab<4>); break;
     default:
-        hipLaunchKernelGGL(k_halo_reduce, g, dim3(T), 0, s, hl, sv, F->sh_ptr.as<int32_t>(),
-                           F->sh_pos.as<int32_t>(), sn, out, out + nv, out + 2 * nv, accumulate, skip);
+        hipLaunchKernelGGL(k_halo_reduce, dim3(grid_n(F->sh_n, T, 1ll << 20)), dim3(T), 0, s, hl, sv,
+                           F->sh_ptr.as<int32_t>(), F->sh_pos.as<int32_t>(), sn, out, out + nv, out + 2 * nv,
+                           accumulate, skip);
     }
     HIPCHK(hipGetLastError());
 }
@@ -1308,6 +1316,7 @@ HaloView elem_halo_view(const ebbx_fem_s *F) {
     h.pos = F->sh_pos.as<int32_t>();
     h.halo = F->halo.as<double>();
     h.nc = F->sh_nc;
+    h.n4 = (int32_t)F->sh_n4;
     return h;
 }
 
@@ -1330,7 +1339,7 @@ bool elem_pre_ok(const ebbx_fem_s *F) {
 }
 
 void elem_pre_prepare(ebbx_fem_s *F, hipStream_t s) {
-    const size_t bytes = std::max<size_t>((size_t)F->halo_n * 9 * sizeof(double), 8);
+    const size_t bytes = (size_t)std::max<int64_t>(F->halo_n, 1) * 9 * sizeof(double);
     if (F->halo9.bytes() != bytes) F->halo9.reset(bytes, s);
 }
 
@@ -1343,8 +1352,8 @@ HaloView elem_pre_halo(const ebbx_fem_s *F) {
 void elem_launch_pre(ebbx_fem_s *F, const double *d, const double *u, double *f, double *y, double *diag,
                      hipStream_t s) {
     if (!elem_pre_ok(F)) fail(EBBX_E_STATE, "the fused step preamble needs the block strategy (one tet per thread)");
-    const size_t need = (size_t)F->halo_n * 9 * sizeof(double);
-    if (F->halo9.bytes() < std::max<size_t>(need, 8)) fail(EBBX_E_STATE, "the fused step preamble's halo is not allocated");
+    const size_t need = (size_t)std::max<int64_t>(F->halo_n, 1) * 9 * sizeof(double);
+    if (F->halo9.bytes() < need) fail(EBBX_E_STATE, "the fused step preamble's halo is not allocated");
     const int64_t nv = F->nv;
     ElemArgs a = base_args(F);
     set_vec(a.d, d, (uint32_t)nv);
@@ -1509,6 +1518,7 @@ void build_halo(ebbx_fem_s *F, const std::vector<int32_t> &verts, const std::vec
     int32_t maxm = 0;
     for (size_t r = 0; r + 1 < sh_ptr.size(); ++r) maxm = std::max(maxm, sh_ptr[r + 1] - sh_ptr[r]);
     F->sh_nc = maxm <= 16 ? std::max(1, (maxm + 3) / 4) : 0;
+    F->sh_n4 = F->sh_nc == 1 ? F->sh_n : 0;   // rows of one width
     if (F->sh_nc > 0) {
         const size_t w = (size_t)4 * F->sh_nc;
         std::vector<int32_t> tab(std::max<size_t>(sh_vert.size() * w, 4), -1);
@@ -1516,7 +1526,7 @@ void build_halo(ebbx_fem_s *F, const std::vector<int32_t> &verts, const std::vec
             for (int32_t j = sh_ptr[r]; j < sh_ptr[r + 1]; ++j) tab[r * w + (size_t)(j - sh_ptr[r])] = sh_pos[(size_t)j];
         upload(F->sh_tab, tab.data(), tab.size() * sizeof(int32_t), s);
     }
-    F->halo.reset(std::max<size_t>((size_t)F->halo_n * 3 * sizeof(double), 8), s);
+    F->halo.reset((size_t)std::max<int64_t>(F->halo_n, 1) * 3 * sizeof(double), s);
 }
 
 // Upload the block tables (without the halo): fixed-stride copies, block b's

@@ -224,13 +224,19 @@ __global__ __launch_bounds__(VT) void k_pair_kp(ElemArgs a, PairArgs c) {
 
 // The halo places of every vertex, W int4 per vertex in block order: -1 padded; all -1 where a
 // block owns the vertex outright; first -2 where no tet touches it.
-__global__ void k_pair_tab(const int32_t *sh_row, const int4 *sh_tab, int64_t nv, int nc, int4 *tab) {
+__global__ void k_pair_tab(HaloView h, int64_t nv, int4 *tab) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nv * nc) return;
-    const int64_t v = i / nc;
-    const int32_t r = sh_row[v];
-    int4 q = r < 0 ? make_int4(-1, -1, -1, -1) : sh_tab[(int64_t)r * nc + (i - v * nc)];
-    if (r >= 0 && i == v * nc && q.x < 0) q.x = -2;
+    if (i >= nv * h.nc) return;
+    const int64_t v = i / h.nc;
+    const int c = (int)(i - v * h.nc);
+    const int32_t r = h.row[v];
+    int4 q = make_int4(-1, -1, -1, -1);
+    if (r >= 0) {
+        int n;
+        const int4 *t = h.at(r, n);
+        if (c < n) q = t[c];
+        if (c == 0 && q.x < 0) q.x = -2;
+    }
     tab[i] = q;
 }
 
@@ -271,17 +277,7 @@ __global__ __launch_bounds__(VT) void k_pair_update(StepVec w, const double *p_n
         } else if (q[0].x != -1) {   // summed from the halo, in block order
             y[0] = y[1] = y[2] = 0.0;
 #pragma unroll
-            for (int i = 0; i < NC; ++i) {
-                const int32_t at[4] = {q[i].x, q[i].y, q[i].z, q[i].w};
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (at[k] >= 0) {
-                        const double *hq = hv.halo + 3 * (size_t)at[k];
-                        y[0] += hq[0];
-                        y[1] += hq[1];
-                        y[2] += hq[2];
-                    }
-            }
+            for (int i = 0; i < NC; ++i) halo_add4(hv.halo, q[i], y);
         }
     }
     if (done) return;   // uniform
@@ -380,8 +376,8 @@ void pair_prepare(ebbx_fem_s *F, hipStream_t s) {
     if (bytes == 0 || F->sh_n == 0) return;
     F->pair_tab.reset(bytes, s);
     const int64_t n = F->nv * F->sh_nc;
-    hipLaunchKernelGGL(k_pair_tab, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, F->sh_row.as<int32_t>(),
-                       F->sh_tab.as<int4>(), F->nv, F->sh_nc, F->pair_tab.as<int4>());
+    hipLaunchKernelGGL(k_pair_tab, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, elem_halo_view(F), F->nv,
+                       F->pair_tab.as<int4>());
     HIPCHK(hipGetLastError());
 }
 

@@ -162,21 +162,16 @@ __device__ __forceinline__ void finished_pre(const HaloView &h, const StepVec &w
     }
 #pragma unroll
     for (int j = 0; j < 9; ++j) o[j] = 0.0;
-    auto add = [&](int32_t pos) {
-        const double *hq = h.halo + 9 * (size_t)pos;
-#pragma unroll
-        for (int j = 0; j < 9; ++j) o[j] += hq[j];
-    };
     if (h.nc > 0) {
-        for (int c = 0; c < h.nc; ++c) {
-            const int4 q = h.tab[(size_t)r * h.nc + c];
-            const int32_t p4[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (p4[k] >= 0) add(p4[k]);
-        }
+        int n;
+        const int4 *t = h.at(r, n);
+        for (int c = 0; c < n; ++c) halo_add(h.halo, t[c], o);
     } else {
-        for (int32_t j = h.ptr[r]; j < h.ptr[r + 1]; ++j) add(h.pos[j]);
+        for (int32_t j = h.ptr[r]; j < h.ptr[r + 1]; ++j) {
+            const double *hq = h.halo + 9 * (size_t)h.pos[j];
+#pragma unroll
+            for (int k = 0; k < 9; ++k) o[k] += hq[k];
+        }
     }
 }
 

@@ -182,40 +182,47 @@ __global__ __launch_bounds__(BT_THREADS) void k_blk_fill(const int32_t *keys, co
 // ---- shared vertices -------------------------------------------------------------------------
 
 // A vertex has a row in the shared-vertex table if it has halo places, or no tet at all (the halo
-// pass zeroes it).  Scan inputs, and the largest number of places of one vertex into *maxm.
-__global__ void k_sh_flags(const int32_t *cnt, const int64_t *rp, int64_t nv, int64_t *flag, int64_t *places,
-                           int *maxm) {
+// pass zeroes it).  Scan inputs (rows, rows of at most 4 places, places), and the largest number of
+// places of one vertex into *maxm.
+__global__ void k_sh_flags(const int32_t *cnt, const int64_t *rp, int64_t nv, int64_t *flag, int64_t *few,
+                           int64_t *places, int *maxm) {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v > nv) return;
     const int32_t c = v < nv ? cnt[v] : 0;
-    flag[v] = v < nv && (c > 0 || rp[v + 1] == rp[v]);
+    const bool on = v < nv && (c > 0 || rp[v + 1] == rp[v]);
+    flag[v] = on;
+    few[v] = on && c <= 4;
     places[v] = c;
     if (c > 0) atomicMax(maxm, c);
 }
 
-__global__ void k_sh_rows(const int32_t *cnt, const int64_t *rp, int64_t nv, const int64_t *row, const int64_t *ptr,
-                          int32_t *sh_vert, int32_t *sh_ptr, int32_t *sh_row) {
+// The rows: nc = 0, in vertex order with offsets ptr into the places (CSR); else the n4 rows of at
+// most 4 places first (one int4 of places each, -1 padded), then the others (nc int4 each), both in
+// vertex order.
+__global__ void k_sh_rows(const int32_t *cnt, const int64_t *rp, int64_t nv, const int64_t *row, const int64_t *few,
+                          const int64_t *ptr, const int32_t *pos, int nc, int32_t *sh_vert, int32_t *sh_ptr,
+                          int32_t *sh_row, int32_t *tab) {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v > nv) return;
     if (v == nv) {
-        sh_ptr[row[nv]] = (int32_t)ptr[nv];
+        if (nc == 0) sh_ptr[row[nv]] = (int32_t)ptr[nv];
         return;
     }
-    const bool on = cnt[v] > 0 || rp[v + 1] == rp[v];
-    sh_row[v] = on ? (int32_t)row[v] : -1;
-    if (on) {
-        sh_vert[row[v]] = (int32_t)v;
-        sh_ptr[row[v]] = (int32_t)ptr[v];
+    const int32_t c = cnt[v];
+    if (c == 0 && rp[v + 1] != rp[v]) {
+        sh_row[v] = -1;
+        return;
     }
-}
-
-// Fixed-width rows of w halo places, -1 padded.
-__global__ void k_sh_tab(const int32_t *sh_ptr, const int32_t *sh_pos, int64_t sh_n, int32_t w, int32_t *tab) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= sh_n * w) return;
-    const int64_t r = i / w;
-    const int32_t j = sh_ptr[r] + (int32_t)(i - r * w);
-    tab[i] = j < sh_ptr[r + 1] ? sh_pos[j] : -1;
+    const int64_t n4 = few[nv], r = nc == 0 ? row[v] : c <= 4 ? few[v] : n4 + row[v] - few[v];
+    sh_row[v] = (int32_t)r;
+    sh_vert[r] = (int32_t)v;
+    if (nc == 0) {
+        sh_ptr[r] = (int32_t)ptr[v];
+        return;
+    }
+    int32_t *t = tab + 4 * (r < n4 ? r : n4 + (r - n4) * nc);
+    const int32_t w = r < n4 ? 4 : 4 * nc;
+    for (int32_t j = 0; j < w; ++j) t[j] = j < c ? pos[ptr[v] + j] : -1;
 }
 
 // Block-local FP32 rest positions: entry (b, i) holds X of block b's i-th vertex minus X of its
@@ -371,37 +378,34 @@ void build_blocks(ebbx_fem_s *F, int32_t bt, bool reorder, hipStream_t s) {
     int bits = 1;
     while ((int64_t(1) << bits) < nv) ++bits;
     radix_sort_pairs_u32(hkey.as<uint32_t>(), F->sh_pos.as<uint32_t>(), nh, bits, s);
-    DevBuf row((size_t)(nv + 1) * sizeof(int64_t), s), ptr((size_t)(nv + 1) * sizeof(int64_t), s);
+    const size_t cols = (size_t)(nv + 1) * sizeof(int64_t);
+    DevBuf row(cols, s), few(cols, s), ptr(cols, s);
     hipLaunchKernelGGL(k_sh_flags, dim3(grid_of(nv + 1, 256)), dim3(256), 0, s, cnt.as<int32_t>(), rp, nv,
-                       row.as<int64_t>(), ptr.as<int64_t>(), mx.as<int>());
+                       row.as<int64_t>(), few.as<int64_t>(), ptr.as<int64_t>(), mx.as<int>());
     HIPCHK(hipGetLastError());
     exclusive_scan_i64(row.as<int64_t>(), nv + 1, s);
+    exclusive_scan_i64(few.as<int64_t>(), nv + 1, s);
     exclusive_scan_i64(ptr.as<int64_t>(), nv + 1, s);
     int maxm = 0;
-    int64_t sh_n = 0;
+    int64_t sh_n = 0, n4 = 0;
     HIPCHK(hipMemcpyAsync(&maxm, mx.as<int>(), sizeof maxm, hipMemcpyDeviceToHost, s));
     HIPCHK(hipMemcpyAsync(&sh_n, row.as<int64_t>() + nv, sizeof sh_n, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(&n4, few.as<int64_t>() + nv, sizeof n4, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    F->sh_n = sh_n;
-    F->sh_vert.reset(room(sh_n, 4), s);
-    F->sh_ptr.reset(room(sh_n + 1, 4), s);
-    F->sh_row.reset(room(nv, 4), s);
-    hipLaunchKernelGGL(k_sh_rows, dim3(grid_of(nv + 1, 256)), dim3(256), 0, s, cnt.as<int32_t>(), rp, nv,
-                       row.as<int64_t>(), ptr.as<int64_t>(), F->sh_vert.as<int32_t>(), F->sh_ptr.as<int32_t>(),
-                       F->sh_row.as<int32_t>());
-    HIPCHK(hipGetLastError());
     // fixed-width rows of halo places when no vertex has more than 16
+    F->sh_n = sh_n;
     F->sh_nc = maxm <= 16 ? std::max(1, (maxm + 3) / 4) : 0;
-    if (F->sh_nc > 0) {
-        const int32_t tw = 4 * F->sh_nc;
-        F->sh_tab.reset(room(sh_n * tw, 4), s);
-        if (sh_n > 0) {
-            hipLaunchKernelGGL(k_sh_tab, dim3(grid_of(sh_n * tw, 256)), dim3(256), 0, s, F->sh_ptr.as<int32_t>(),
-                               F->sh_pos.as<int32_t>(), sh_n, tw, F->sh_tab.as<int32_t>());
-            HIPCHK(hipGetLastError());
-        }
-    }
-    F->halo.reset(std::max<size_t>((size_t)nh * 3 * sizeof(double), 8), s);
+    F->sh_n4 = F->sh_nc > 0 ? n4 : 0;
+    F->sh_vert.reset(room(sh_n, 4), s);
+    F->sh_row.reset(room(nv, 4), s);
+    if (F->sh_nc == 0) F->sh_ptr.reset(room(sh_n + 1, 4), s);
+    else F->sh_tab.reset(room(n4 + (sh_n - n4) * F->sh_nc, 16), s);
+    hipLaunchKernelGGL(k_sh_rows, dim3(grid_of(nv + 1, 256)), dim3(256), 0, s, cnt.as<int32_t>(), rp, nv,
+                       row.as<int64_t>(), few.as<int64_t>(), ptr.as<int64_t>(), F->sh_pos.as<int32_t>(), F->sh_nc,
+                       F->sh_vert.as<int32_t>(), F->sh_ptr.as<int32_t>(), F->sh_row.as<int32_t>(),
+                       F->sh_tab.as<int32_t>());
+    HIPCHK(hipGetLastError());
+    F->halo.reset((size_t)std::max<int64_t>(nh, 1) * 3 * sizeof(double), s);
     HIPCHK(hipStreamSynchronize(s));   // the scratch above is freed on return
     F->halo_level = 0;
     F->blocks_built = true;
