@@ -108,13 +108,15 @@ __global__ __launch_bounds__(VT) void k_pair_kp(ElemArgs a, PairArgs c) {
     T *s_h = REUSE ? (T *)s_dyn4 : XF ? (T *)(s_xf + ((3 * S + 3) & ~3u)) : (T *)(s_x + (XB ? 3 * S : 0));
 
     const int32_t gvs0 = tid < S ? bverts[tid] : -1;
-    const bool has = gvs0 >= 0;
-    const uint32_t gv0 = has ? (uint32_t)gvs0 : 0u;
     int32_t hp0 = -1, j00 = 0, j10 = 0;
-    if (has) {
+    float f0[3] = {0.0f, 0.0f, 0.0f};
+    if (tid < S) {   // as in block_body, before the vertex id is waited for
         hp0 = bhpos[tid];
         j00 = brow[tid];
         j10 = brow[tid + 1];
+        if (XF)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) f0[k] = a.xf[k][(size_t)blk * S + tid];
     }
     T b[9], V0 = T(1), mu = T(0), lam = T(0);
     uint32_t sl[4] = {0, 0, 0, 0}, pw[2] = {0, 0};
@@ -136,16 +138,16 @@ __global__ __launch_bounds__(VT) void k_pair_kp(ElemArgs a, PairArgs c) {
         pw[1] = ldc<uint32_t>(a.blk_pos[1], t);
     }
     // the first block vertex's fields are in flight while the partials are summed
+    const bool has = gvs0 >= 0;
+    const uint32_t gv0 = has ? (uint32_t)gvs0 : 0u;
     double d0[3], x0[3], z0[3], p0[3];
-    float f0[3];
     if (has)
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             z0[k] = ldc<double>(a.u[k], gv0);
             p0[k] = FIRST ? 0.0 : ldc<double>(c.p_old + (size_t)k * a.nv, gv0);
             d0[k] = ldc<double>(a.d[k], gv0);
-            if (XF) f0[k] = a.xf[k][(size_t)blk * S + tid];
-            else if (XB) x0[k] = ldc<double>(a.X[k], gv0);
+            if (XB && !XF) x0[k] = ldc<double>(a.X[k], gv0);
         }
     if (done || !pair_beta<FIRST>(c, s12, rz, rr, beta)) return;   // the same sums in every workgroup
     if (has)
