@@ -447,22 +447,27 @@ __global__ void k_edge_heads(const uint64_t *key, int64_t n, int64_t *flag) {
         flag[i] = i < n && (i == 0 || key[i] != key[i - 1]);
 }
 
-// at[i]: edges before entry i.  The first entry of an edge writes its head and its entries' start;
-// the first entry of a tail also the row offsets up to that tail, the last entry those after it.
-__global__ void k_edge_fill(const uint64_t *key, const int64_t *at, int64_t n, int64_t nv, int shift, int32_t *row,
-                            int32_t *col, int32_t *gptr) {
+// at[i]: edges before entry i.  The first entry of an edge writes its head and its entries' start.
+__global__ void k_edge_fill(const uint64_t *key, const int64_t *at, int64_t n, int shift, int32_t *col, int32_t *gptr) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const uint64_t k = key[i];
-        const int64_t tail = (int64_t)(k >> shift), before = i > 0 ? (int64_t)(key[i - 1] >> shift) : -1;
         if (at[i + 1] != at[i]) {
-            col[at[i]] = (int32_t)(k & ((1ull << shift) - 1ull));
+            col[at[i]] = (int32_t)(key[i] & ((1ull << shift) - 1ull));
             gptr[at[i]] = (int32_t)i;
         }
-        for (int64_t v = before + 1; v <= tail; ++v) row[v] = (int32_t)at[i];
-        if (i == n - 1) {
-            for (int64_t v = tail + 1; v <= nv; ++v) row[v] = (int32_t)at[n];
-            gptr[at[n]] = (int32_t)n;
+        if (i == n - 1) gptr[at[n]] = (int32_t)n;
+    }
+}
+
+// row[v]: edges whose tail is below v.
+__global__ void k_edge_rows(const uint64_t *key, const int64_t *at, int64_t n, int64_t nv, int shift, int32_t *row) {
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v <= nv; v += (int64_t)gridDim.x * blockDim.x) {
+        int64_t lo = 0, hi = n;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if ((int64_t)(key[mid] >> shift) < v) lo = mid + 1;
+            else hi = mid;
         }
+        row[v] = (int32_t)at[lo];
     }
 }
 
@@ -602,8 +607,11 @@ void build_edges(ebbx_fem_s *F, hipStream_t s) {
         HIPCHK(hipStreamSynchronize(s));
         F->e_col.reset(room(ne, 4), s);
         F->e_gptr.reset(room(ne + 1, 4), s);
-        hipLaunchKernelGGL(k_edge_fill, grid(n), dim3(256), 0, s, key.as<uint64_t>(), at.as<int64_t>(), n, nv, shift,
-                           F->e_row.as<int32_t>(), F->e_col.as<int32_t>(), F->e_gptr.as<int32_t>());
+        hipLaunchKernelGGL(k_edge_fill, grid(n), dim3(256), 0, s, key.as<uint64_t>(), at.as<int64_t>(), n, shift,
+                           F->e_col.as<int32_t>(), F->e_gptr.as<int32_t>());
+        HIPCHK(hipGetLastError());
+        hipLaunchKernelGGL(k_edge_rows, grid(nv + 1), dim3(256), 0, s, key.as<uint64_t>(), at.as<int64_t>(), n, nv,
+                           shift, F->e_row.as<int32_t>());
         HIPCHK(hipGetLastError());
         HIPCHK(hipStreamSynchronize(s));
     } else {

@@ -7,11 +7,11 @@
 // does not own outright get a place in the halo; the shared-vertex tables list each
 // such vertex's halo places in block order.
 //
-// One workgroup sorts a block's 4 bt (vertex, incidence) pairs in LDS, once to count
-// (vertices per block fix the tables' stride, shared vertices the halo's places) and
-// once to write: sorting 8 KiB in LDS twice costs less than keeping the sorted pairs
-// of every block in memory between the passes.  Bound by the barriers of the sort's
-// stages.  The tables equal those of host_blocks (elem.hip) entry for entry.
+// One workgroup sorts a block's 4 bt (vertex, incidence) pairs in LDS and counts
+// (vertices per block fix the tables' stride, shared vertices the halo's places); a
+// second pass writes the tables from the sorted pairs, 32 bytes per tet kept in
+// memory between the two (sorting again instead took 75 us of the second pass's 80,
+// 2,000 blocks).  Bound by the barriers of the sort's stages.  The tables equal those of host_blocks (elem.hip) entry for entry.
 // Measured, a new scrambled mesh of 358k tets taken in (relations, Morton order, domain,
 // mass, one force; FP32): 71.9 ms with the tables built on the host and each pass of the
 // radix sort waited for, 1.60 ms with these.
@@ -94,12 +94,13 @@ __device__ __forceinline__ void each_head(const unsigned long long *s, int32_t n
 // Pass 1: the block's shared vertices into nsh[b], the largest vertex count of a block into *maxv,
 // all blocks' vertices together into *staged.
 __global__ __launch_bounds__(BT_THREADS) void k_blk_count(const int32_t *keys, const int64_t *rp, int64_t nt,
-                                                          int32_t bt, int32_t n, int64_t *nsh, int *maxv,
-                                                          unsigned long long *staged) {
+                                                          int32_t bt, int32_t n, unsigned long long *pairs,
+                                                          int64_t *nsh, int *maxv, unsigned long long *staged) {
     extern __shared__ unsigned long long s_pairs[];
     __shared__ int32_t sw[BT_THREADS / 64];
     const int64_t b = blockIdx.x;
     sorted_pairs(keys, nt, b, bt, n, s_pairs);
+    for (int32_t e = threadIdx.x; e < 4 * bt; e += BT_THREADS) pairs[b * 4 * bt + e] = s_pairs[e];
     int32_t heads = 0, shared = 0;
     each_head(s_pairs, n, rp, [&](int32_t, uint32_t, int32_t, bool sh) {
         ++heads;
@@ -124,15 +125,16 @@ struct BlkOut {
 };
 
 // Pass 2: the tables of block b; its halo places start at hbase[b].
-__global__ __launch_bounds__(BT_THREADS) void k_blk_fill(const int32_t *keys, const int64_t *rp, int64_t nt,
-                                                         int32_t bt, int32_t n, int32_t S, int32_t w,
+__global__ __launch_bounds__(BT_THREADS) void k_blk_fill(const unsigned long long *pairs, const int64_t *rp,
+                                                         int64_t nt, int32_t bt, int32_t n, int32_t S, int32_t w,
                                                          const int64_t *hbase, BlkOut o) {
     extern __shared__ unsigned long long s_pairs[];
     uint32_t *s_at = (uint32_t *)(s_pairs + n);   // per incidence: slot << 16 | row
     __shared__ int32_t sw[BT_THREADS / 64];
     const int64_t b = blockIdx.x;
     const int tid = threadIdx.x;
-    sorted_pairs(keys, nt, b, bt, n, s_pairs);
+    for (int32_t e = tid; e < n; e += BT_THREADS) s_pairs[e] = e < 4 * bt ? pairs[b * 4 * bt + e] : ~0ull;
+    __syncthreads();
     int32_t heads = 0, shared = 0;
     each_head(s_pairs, n, rp, [&](int32_t, uint32_t, int32_t, bool sh) {
         ++heads;
@@ -258,6 +260,7 @@ namespace {
 // What pass 1 finds about blocks of bt tets with the keys in a given order.
 struct Counted {
     DevBuf hbase;         // nblk + 1: first halo place of each block
+    DevBuf pairs;         // 4 bt sorted pairs per block
     int32_t maxv = 1;     // largest vertex count of a block
     int64_t halo = 0, staged = 0;
 };
@@ -273,12 +276,14 @@ Counted count_blocks(const int32_t *keys, const int64_t *rp, int64_t nt, int32_t
     const int64_t nblk = (nt + bt - 1) / bt;
     const int32_t n = pairs_of(bt);
     c.hbase.reset((size_t)(nblk + 1) * sizeof(int64_t), s);
+    c.pairs.reset(std::max<size_t>((size_t)nblk * 4 * bt * sizeof(unsigned long long), 16), s);
     DevBuf mx(16, s);
     HIPCHK(hipMemsetAsync(mx.get(), 0, 16, s));
     HIPCHK(hipMemsetAsync(c.hbase.get(), 0, c.hbase.bytes(), s));
     if (nblk > 0) {
         hipLaunchKernelGGL(k_blk_count, dim3((unsigned)nblk), dim3(BT_THREADS), (size_t)n * 8, s, keys, rp, nt, bt, n,
-                           c.hbase.as<int64_t>(), mx.as<int>(), mx.as<unsigned long long>() + 1);
+                           c.pairs.as<unsigned long long>(), c.hbase.as<int64_t>(), mx.as<int>(),
+                           mx.as<unsigned long long>() + 1);
         HIPCHK(hipGetLastError());
     }
     exclusive_scan_i64(c.hbase.as<int64_t>(), nblk + 1, s);
@@ -317,8 +322,7 @@ void build_blocks(ebbx_fem_s *F, int32_t bt, bool reorder, hipStream_t s) {
     F->ordered = false;
     F->B_ord.release();
     F->mat_ord.release();
-    const int32_t *keys = F->keys;
-    Counted c = count_blocks(keys, rp, nt, bt, s);
+    Counted c = count_blocks(F->keys, rp, nt, bt, s);
     F->order_settled = reorder || c.maxv <= 256;
     // Blocks of more than 256 vertices share few of them between their tets (a Morton or lattice
     // order of a tet mesh has 100 to 180 in a block of 256 tets): the tables then follow a locality
@@ -338,7 +342,6 @@ void build_blocks(ebbx_fem_s *F, int32_t bt, bool reorder, hipStream_t s) {
         Counted o = count_blocks(okeys.as<int32_t>(), rp, nt, bt, s);
         if (o.staged * 5 <= c.staged * 4) {
             F->ordered = true;
-            keys = okeys.as<int32_t>();
             c = std::move(o);
         }
     }
@@ -362,8 +365,8 @@ void build_blocks(ebbx_fem_s *F, int32_t bt, bool reorder, hipStream_t s) {
         const BlkOut o{F->blk_verts.as<int32_t>(), F->blk_hpos.as<int32_t>(), F->blk_lptr.as<uint16_t>(),
                        F->blk_pos.as<uint32_t>(), F->blk_local.as<uint32_t>(), hkey.as<uint32_t>(),
                        F->sh_pos.as<uint32_t>(), cnt.as<int32_t>()};
-        hipLaunchKernelGGL(k_blk_fill, dim3((unsigned)nblk), dim3(BT_THREADS), (size_t)n * 12, s, keys, rp, nt, bt, n,
-                           S, w, c.hbase.as<int64_t>(), o);
+        hipLaunchKernelGGL(k_blk_fill, dim3((unsigned)nblk), dim3(BT_THREADS), (size_t)n * 12, s,
+                           c.pairs.as<unsigned long long>(), rp, nt, bt, n, S, w, c.hbase.as<int64_t>(), o);
         HIPCHK(hipGetLastError());
     }
     F->blk_tets = bt;
