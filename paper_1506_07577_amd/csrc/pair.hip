@@ -369,7 +369,8 @@ void launch_kp(const ebbx_fem_s *F, const ElemArgs &a, const PairArgs &c, bool f
 
 bool pair_ok(const ebbx_fem_s *F) {
     return F->nm == 1 && F->strategy == EBBX_STRAT_BLOCK && F->blk_red == 0 && F->blk_tpt == 1 &&
-           F->blk_tets == VT && F->halo_level == 0 && F->nt > 0 && F->nblk <= PAIR_BLOCKS;
+           F->blk_tets == VT && F->halo_level == 0 && F->nt > 0 &&
+           F->nblk <= (F->prec == EBBX_F32 ? PAIR_BLOCKS_F32 : PAIR_BLOCKS);
 }
 
 void pair_prepare(ebbx_fem_s *F, hipStream_t s) {

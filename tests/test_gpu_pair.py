@@ -69,6 +69,11 @@ def test_fixed_count(name, model, prec):
         assert _both(MESHES[name](), model, prec, maxit, 0.0, damped=maxit == 7) <= bound
 
 
+@pytest.mark.parametrize("n", [27, 28])   # 462 and 515 blocks: either side of the limit of FP32 elements
+def test_f32_limit(n):
+    assert _both(mg.jitter(mg.kuhn_cube(n), 0.01, seed=0), 1, "f32", 3, 0.0) <= 1e-5
+
+
 @pytest.mark.parametrize("tol", [1e-3, 1e-11, 1e-14])
 def test_to_a_tolerance(tol):
     m = mg.jitter(mg.kuhn_cube(13), 0.01, seed=0)
