@@ -326,7 +326,8 @@ void build_blocks(ebbx_fem_s *F, int32_t bt, bool reorder, hipStream_t s) {
     F->order_settled = reorder || c.maxv <= 256;
     // Blocks of more than 256 vertices share few of them between their tets (a Morton or lattice
     // order of a tet mesh has 100 to 180 in a block of 256 tets): the tables then follow a locality
-    // order of the tets instead of the rows' own, if that stages at least a fifth fewer vertices.
+    // order of the tets instead of the rows' own, if that stages at least a fifth fewer vertices and
+    // needs no more LDS and halo than the rows' order (so no call meets a limit that it did not).
     // Measured, force and K u, a scrambled mesh of 635k tets, StVK FP64: 272 us in the rows' order
     // (blocks of 1,000 vertices, every vertex in some 24 of them), 55 us in the locality order.
     // Where the rows' order gives blocks of at most 256 vertices there is nothing to gain: lattice
@@ -340,7 +341,7 @@ void build_blocks(ebbx_fem_s *F, int32_t bt, bool reorder, hipStream_t s) {
         okeys.reset((size_t)4 * nt * sizeof(int32_t), s);
         permute_columns(F->keys, okeys.get(), 4, F->t_order.as<int32_t>(), nt, 4, s);
         Counted o = count_blocks(okeys.as<int32_t>(), rp, nt, bt, s);
-        if (o.staged * 5 <= c.staged * 4) {
+        if (o.staged * 5 <= c.staged * 4 && o.maxv <= c.maxv && o.halo <= c.halo) {
             F->ordered = true;
             c = std::move(o);
         }
