@@ -32,7 +32,8 @@ constexpr int64_t PAIR_BLOCKS_F32 = 512;
 // Whether F's solves run so: one mesh, BLOCK strategy with 256 tets per block, one per thread,
 // incidence-order sums, at most PAIR_BLOCKS blocks (FP32 elements: PAIR_BLOCKS_F32).
 bool pair_ok(const ebbx_fem_s *F);
-// The per-vertex halo places that the iterations read (pair_tab), before they are captured.
+// The per-vertex halo places that the iterations read (pair_tab), whole on return; before they are
+// captured.
 void pair_prepare(ebbx_fem_s *F, hipStream_t s);
 // `count` iterations (at most maxit) from an even iteration onto stream s; first: from the solve's
 // first one.  part_k: one double per tet block.

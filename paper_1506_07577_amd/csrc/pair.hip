@@ -374,7 +374,7 @@ bool pair_ok(const ebbx_fem_s *F) {
 }
 
 void pair_prepare(ebbx_fem_s *F, hipStream_t s) {
-    F->pair_tab.release();
+    if (F->pair_tab.get()) return;   // of the present tables; an earlier solve may still be reading it
     const size_t bytes = (size_t)F->nv * F->sh_nc * sizeof(int4);
     if (bytes == 0 || F->sh_n == 0) return;
     F->pair_tab.reset(bytes, s);
@@ -382,6 +382,7 @@ void pair_prepare(ebbx_fem_s *F, hipStream_t s) {
     hipLaunchKernelGGL(k_pair_tab, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, elem_halo_view(F), F->nv,
                        F->pair_tab.as<int4>());
     HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(s));   // the solve that reads it runs on another stream
 }
 
 void pair_iterations(ebbx_fem_s *F, const ebbx_step_params &p, const StepVec &w, CGState *st, SolveCtl *ctl,

@@ -1025,7 +1025,8 @@ void build_graphs(ebbx_fem_s *F, const ebbx_step_params &p, int mode) {
     if (S.pre[mode]) return;
     // the two-kernel iterations' block partials and halo places, allocated outside the capture
     if (pair_ok(F) && !S.valid) {
-        S.part_k.reset((size_t)F->nblk * sizeof(double), S.cap);
+        const size_t bytes = (size_t)F->nblk * sizeof(double);
+        if (S.part_k.bytes() != bytes) S.part_k.reset(bytes, S.cap);   // kept: an earlier solve may still use it
         pair_prepare(F, S.cap);
     }
     const SolveBufs b = step_bufs(F);

@@ -106,3 +106,30 @@ def test_not_converged_and_breakdown():
     st = ebbx.stats_fetch(mesh.fem.implicit_step(d, v, 1e-2, maxit=50, precond=ebbx.PRECOND_NONE))
     assert st.status == ebbx.E_NOT_SPD
     assert torch.equal(d, d0) and torch.equal(v, v0)
+
+
+def test_streams_and_parameters():
+    """A new domain's first solve on a stream of its own, parameters changed (graphs rebuilt) and
+    strategies set between calls that nobody waits for: the states are those of calls waited for one
+    by one, bit for bit."""
+    m = mg.jitter(mg.kuhn_cube(13), 0.01, seed=0)
+    d0, v0 = mg.perturbed_state(m, 0.02, seed=10), 0.05 * mg.direction(m, 11)
+
+    def run(stream, wait):
+        mesh = ebbx.FemMesh(m.X, m.tets, m.pinned, model=1, elem_prec=ebbx.F64, E=1e5, nu=0.3,
+                            strategy=ebbx.STRAT_BLOCK)
+        d, v = mesh.to_dev(d0), mesh.to_dev(v0)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            for dt in (1e-3, 5e-4, 1e-3):
+                mesh.fem.implicit_step(d, v, dt, tol=0.0, maxit=40)
+                if wait:
+                    torch.cuda.synchronize()
+            mesh.fem.set_strategy(ebbx.STRAT_BLOCK, 128)
+            mesh.fem.set_strategy(ebbx.STRAT_BLOCK, 256)
+            mesh.fem.implicit_step(d, v, 1e-3, tol=0.0, maxit=40)
+        torch.cuda.synchronize()
+        return d, v
+
+    want, got = run(torch.cuda.current_stream(), True), run(torch.cuda.Stream(), False)
+    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
