@@ -302,7 +302,7 @@ void build_pipe(ebbx_fem_s *F, int32_t g, hipStream_t s) {
         sv_ptr.push_back((int32_t)sv_all.size());
     }
     std::vector<int32_t> hpos;
-    tables_begin(F);
+    F->pair_tab.release();
     F->ordered = false;   // over the rows' own order
     build_halo(F, sv_all, own_all, rp, hpos, s);
     upload_block_tables(F, hb, {}, s);

@@ -311,18 +311,13 @@ void refresh_ordered(ebbx_fem_s *F, hipStream_t s) {
     }
 }
 
-void tables_begin(ebbx_fem_s *F) {
-    if (F->blk_verts.get()) HIPCHK(hipDeviceSynchronize());
-    F->pair_tab.release();
-}
-
 void build_blocks(ebbx_fem_s *F, int32_t bt, bool reorder, hipStream_t s) {
     if (bt < 64 || bt > 1024 || bt % 64)
         fail(EBBX_E_ARG, "block strategy: tets per block must be a multiple of 64 from 64 to 1024 (got %d)", bt);
     const int64_t nt = F->nt, nv = F->nv, nblk = (nt + bt - 1) / bt;
     const int64_t *rp = F->group->row_ptr.as<int64_t>();
     const int32_t n = pairs_of(bt);
-    tables_begin(F);
+    F->pair_tab.release();
     F->blocks_built = false;   // until the tables below are whole
     F->halo_level = -1;
     F->ordered = false;
