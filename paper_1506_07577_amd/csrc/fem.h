@@ -42,6 +42,7 @@ struct ActList {
 __host__ __device__ inline ActList act_list(const int32_t *p, int32_t nm) {
     return ActList{p, p + 4, p + 4 + (nm + 1)};
 }
+constexpr int32_t ACT_OWN = 256;   // meshes of a batch whose list every workgroup forms for itself
 inline size_t act_list_ints(int64_t nm) { return (size_t)(4 + (nm + 1) + nm); }
 
 // Everything an element kernel reads; plain pointers, passed by value.  Column
@@ -95,6 +96,7 @@ struct ElemArgs {
                                 // all finished returns at once (block strategies)
     const int32_t *act;         // nullable: the active list of a batched solve (k_block_list)
     int32_t act_nm;             // meshes of that batch (the list's array stride)
+    const int4 *act_mesh;       // nullable: the meshes' blocks, for workgroups that form the list themselves
     // the fused step preamble (k_block_pre): f, K u and the stiffness diagonal, each into three
     // columns; shared vertices' partials go to halo9, 9 per entry (f, then K u, then diagonal)
     double *pre_out[3][3];
@@ -114,6 +116,9 @@ void elem_launch(ebbx_fem_s *F, ElemOp op, const double *d, const double *u, dou
 // The arguments of a BLOCK-strategy kernel of map `op` (its shared vertices left in the domain's
 // halo), and the dynamic LDS it needs; fails if a workgroup cannot hold it.
 ElemArgs elem_block_args(ebbx_fem_s *F, ElemOp op, const double *d, const double *u, double *out, size_t *shmem);
+// The table from which the workgroups of a small batch's list kernel form the list (F->act_mesh),
+// whole on return; before they are captured.  tptr: the meshes' tet offsets.
+void act_prepare(ebbx_fem_s *F, const int64_t *tptr, hipStream_t s);
 // Whether the element map `op` of F's strategy can run over an active list (act of
 // elem_launch, batches only): the stiffness product of the BLOCK strategy, one tet per thread.
 bool elem_list_ok(const ebbx_fem_s *F, ElemOp op);
@@ -294,6 +299,7 @@ struct ebbx_fem_s {
     ebbx::DevBuf blk_xf;   // block-local FP32 rest positions (FP32 elements, blocks of <= 256 vertices)
     ebbx::DevBuf blk_verts, blk_lptr, blk_pos, blk_hpos, blk_local, halo, sh_vert, sh_ptr, sh_pos, sh_tab,
         sh_row;
+    ebbx::DevBuf act_mesh;     // batches of at most ACT_OWN meshes: their blocks (act_prepare; else empty)
     ebbx::DevBuf pair_tab;     // per-vertex halo places of the two-kernel CG iterations
     ebbx::DevBuf halo9;        // the fused step preamble's halo (9 values per entry)
     int32_t sh_nc = 0;         // int4 chunks per row of sh_tab (0: use the CSR form)

@@ -303,6 +303,7 @@ void build_pipe(ebbx_fem_s *F, int32_t g, hipStream_t s) {
     }
     std::vector<int32_t> hpos;
     F->pair_tab.release();
+    F->act_mesh.release();
     F->ordered = false;   // over the rows' own order
     build_halo(F, sv_all, own_all, rp, hpos, s);
     upload_block_tables(F, hb, {}, s);

@@ -65,7 +65,8 @@ static unsigned grid_one(int nch, int cpw) { return (unsigned)((nch + cpw - 1) /
 static unsigned grid_for(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (n + VT - 1) / VT)); }
 
 // Rebuild the active list (ActList) of a batched solve from the meshes' finished flags, at the
-// start of a CG iteration; one workgroup.  Mesh m's tets are [tptr[m], tptr[m+1]), its blocks
+// start of a CG iteration, where a batch has too many meshes for the product's workgroups to form it
+// themselves (act_prepare); one workgroup.  Mesh m's tets are [tptr[m], tptr[m+1]), its blocks
 // of bt tets those holding them; its first block is left to an earlier unfinished mesh with
 // tets in that block, if there is one (small meshes can share a block with several others).
 // Scans are in mesh order, so the list is the same on every run.
@@ -967,7 +968,7 @@ void launch_iterations(ebbx_fem_s *F, const ebbx_step_params &p, const SolveBufs
     // one mesh: the vector kernels take their chunk from blockIdx alone
     const bool one = b.nm == 1;
     for (int it = 0; it < count && it < p.maxit; ++it) {
-        if (list) {
+        if (list && !F->act_mesh.get()) {
             hipLaunchKernelGGL(k_active, dim3(1), dim3(VT), 0, cs, (const SolveCtl *)ctl, b.tptr, F->tmesh,
                                (int32_t)b.nm, (int32_t)F->blk_tets, b.act);
         }
@@ -1029,6 +1030,7 @@ void build_graphs(ebbx_fem_s *F, const ebbx_step_params &p, int mode) {
         if (S.part_k.bytes() != bytes) S.part_k.reset(bytes, S.cap);   // kept: an earlier solve may still use it
         pair_prepare(F, S.cap);
     }
+    if (S.nm > 1 && !S.valid) act_prepare(F, S.tptr.as<int64_t>(), S.cap);
     const SolveBufs b = step_bufs(F);
     hipStream_t cs = S.cap;
     if (pre_fused(F, p, mode)) elem_pre_prepare(F, cs);   // its halo, allocated outside the capture

@@ -318,6 +318,7 @@ void build_blocks(ebbx_fem_s *F, int32_t bt, bool reorder, hipStream_t s) {
     const int64_t *rp = F->group->row_ptr.as<int64_t>();
     const int32_t n = pairs_of(bt);
     F->pair_tab.release();
+    F->act_mesh.release();
     F->blocks_built = false;   // until the tables below are whole
     F->halo_level = -1;
     F->ordered = false;
