@@ -331,8 +331,8 @@ __global__ void k_key_range(const int32_t *keys, int64_t n, int64_t nmax, unsign
 // ---- grouping -------------------------------------------------------------------------
 
 // rp[v] = incidences whose key is below v: a binary search of the sorted keys per row.  Counting the
-// keys with atomics took 64 us for the 358k tets of a 44^3 mesh, and 11 ms where the keys are a
-// batch's few meshes.
+// keys with atomics took 64 us for the tets of a mesh of 47 x 44 x 41 cells, and 11 ms where the keys
+// are the 48 meshes of a batch; this takes 9.4 us, and at most 49.
 __global__ void k_group_rows(const uint32_t *keys, int64_t total, int64_t n_target, int64_t *rp) {
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v <= n_target;
          v += (int64_t)gridDim.x * blockDim.x) {
