@@ -59,7 +59,7 @@ __device__ __forceinline__ void pair_record(const PairArgs &c, double rz, double
 
 // Workgroups [0, nblk): tet blocks (XCD x one contiguous range); from wg0 (a multiple of 8, so the
 // chunks keep the XCDs of their blocks): vertex chunks.
-template <class T, int MODEL, int W, bool FIRST>
+template <int MODEL, int W, bool FIRST>
 __global__ __launch_bounds__(VT) void k_pair_kp(ElemArgs a, PairArgs c) {
     extern __shared__ uint4 s_dyn4[];
     __shared__ double s12[12];
@@ -102,36 +102,30 @@ __global__ __launch_bounds__(VT) void k_pair_kp(ElemArgs a, PairArgs c) {
     const int32_t *bhpos = a.blk_hpos + (size_t)blk * S;
     const uint16_t *brow = a.blk_row + (size_t)blk * (S + 1);
     // the LDS layout of the stiffness product's block kernel
-    constexpr bool XB = W == 1, XF = XB && sizeof(T) == 4, REUSE = sizeof(T) == 8;
-    double *s_d = (double *)s_dyn4, *s_p = s_d + 3 * S, *s_x = s_p + 3 * S;
-    float *s_xf = (float *)s_x;
-    T *s_h = REUSE ? (T *)s_dyn4 : XF ? (T *)(s_xf + ((3 * S + 3) & ~3u)) : (T *)(s_x + (XB ? 3 * S : 0));
+    constexpr bool XB = W == 1;
+    double *s_d = (double *)s_dyn4, *s_p = s_d + 3 * S, *s_x = s_p + 3 * S, *s_h = s_d;
 
     const int32_t gvs0 = tid < S ? bverts[tid] : -1;
     int32_t hp0 = -1, j00 = 0, j10 = 0;
-    float f0[3] = {0.0f, 0.0f, 0.0f};
     if (tid < S) {   // as in block_body, before the vertex id is waited for
         hp0 = bhpos[tid];
         j00 = brow[tid];
         j10 = brow[tid + 1];
-        if (XF)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) f0[k] = a.xf[k][(size_t)blk * S + tid];
     }
-    T b[9], V0 = T(1), mu = T(0), lam = T(0);
+    double b[9], V0 = 1.0, mu = 0.0, lam = 0.0;
     uint32_t sl[4] = {0, 0, 0, 0}, pw[2] = {0, 0};
     if (in) {
         if (!XB) {
 #pragma unroll
-            for (int k = 0; k < 9; ++k) b[k] = ldc<T>(a.B[k], t);
+            for (int k = 0; k < 9; ++k) b[k] = ldc<double>(a.B[k], t);
             V0 = tet_V0(b);
         }
         if (a.mu_t) {
-            mu = ldc<T>(a.mu_t, t);
-            lam = ldc<T>(a.lam_t, t);
+            mu = ldc<double>(a.mu_t, t);
+            lam = ldc<double>(a.lam_t, t);
         } else {
-            mu = (T)a.mu;
-            lam = (T)a.lam;
+            mu = a.mu;
+            lam = a.lam;
         }
         unpack_slots<W>(a, t, sl);
         pw[0] = ldc<uint32_t>(a.blk_pos[0], t);
@@ -147,7 +141,7 @@ __global__ __launch_bounds__(VT) void k_pair_kp(ElemArgs a, PairArgs c) {
             z0[k] = ldc<double>(a.u[k], gv0);
             p0[k] = FIRST ? 0.0 : ldc<double>(c.p_old + (size_t)k * a.nv, gv0);
             d0[k] = ldc<double>(a.d[k], gv0);
-            if (XB && !XF) x0[k] = ldc<double>(a.X[k], gv0);
+            if (XB) x0[k] = ldc<double>(a.X[k], gv0);
         }
     if (done || !pair_beta<FIRST>(c, s12, rz, rr, beta)) return;   // the same sums in every workgroup
     if (has)
@@ -155,8 +149,7 @@ __global__ __launch_bounds__(VT) void k_pair_kp(ElemArgs a, PairArgs c) {
         for (int k = 0; k < 3; ++k) {
             s_d[k * S + tid] = d0[k];
             s_p[k * S + tid] = z0[k] + beta * p0[k];
-            if (XF) s_xf[k * S + tid] = f0[k];
-            else if (XB) s_x[k * S + tid] = x0[k];
+            if (XB) s_x[k * S + tid] = x0[k];
         }
     for (uint32_t i = tid + VT; i < S; i += VT) {
         const int32_t gvs = bverts[i];
@@ -166,46 +159,25 @@ __global__ __launch_bounds__(VT) void k_pair_kp(ElemArgs a, PairArgs c) {
         for (int k = 0; k < 3; ++k) {
             s_d[k * S + i] = ldc<double>(a.d[k], gv);
             s_p[k * S + i] = ldc<double>(a.u[k], gv) + (FIRST ? 0.0 : beta * ldc<double>(c.p_old + (size_t)k * a.nv, gv));
-            if (XF) s_xf[k * S + i] = a.xf[k][(size_t)blk * S + i];
-            else if (XB) s_x[k * S + i] = ldc<double>(a.X[k], gv);
+            if (XB) s_x[k * S + i] = ldc<double>(a.X[k], gv);
         }
     }
     __syncthreads();
     const uint32_t q[4] = {pw[0] & 0xffffu, pw[0] >> 16, pw[1] & 0xffffu, pw[1] >> 16};
     double pk = 0.0;   // this tet's share of p.Kp
-    T h[12];
-    if (REUSE) {
-        T G[9], dF[9];
-        if (in) {
-            if (XB) rest_B(s_x, S, sl, b, V0);
-            staged_grad(s_d, S, sl, b, G);
-            staged_grad(s_p, S, sl, b, dF);
-        }
-        __syncthreads();   // the rows overwrite the staging
-        if (in) {
-            T dP[9];
-            dstress_scaled<T, MODEL>(mu, lam, V0, G, dF, dP);
-            corner_out(dP, b, h);
+    double h[12], G[9], dF[9];
+    if (in) {
+        if (XB) rest_B(s_x, S, sl, b, V0);
+        staged_grad(s_d, S, sl, b, G);
+        staged_grad(s_p, S, sl, b, dF);
+    }
+    __syncthreads();   // the rows overwrite the staging
+    if (in) {
+        double dP[9];
+        dstress_scaled<double, MODEL>(mu, lam, V0, G, dF, dP);
+        corner_out(dP, b, h);
 #pragma unroll
-            for (int k = 0; k < 9; ++k) pk += (double)dF[k] * (double)dP[k];   // = the corners' sum below
-        }
-    } else if (in) {
-        double qd[4][3], qp[4][3];
-#pragma unroll
-        for (int k4 = 0; k4 < 4; ++k4)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                qd[k4][k] = s_d[k * S + sl[k4]];
-                qp[k4][k] = s_p[k * S + sl[k4]];
-            }
-        if constexpr (XF) rest_B_local(s_xf, S, sl, b, V0);
-        else if (XB) rest_B(s_x, S, sl, b, V0);
-        eval_tet<T, MODEL, OP_KMUL>(mu, lam, b, V0, qd, qp, h, qp);
-        // FP32 corner results against FP64 p, as the vertex sums would meet it
-#pragma unroll
-        for (int k4 = 0; k4 < 4; ++k4)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) pk += (double)h[3 * k4 + k] * qp[k4][k];
+        for (int k = 0; k < 9; ++k) pk += dF[k] * dP[k];   // = the corners' sum against p
     }
     if (in)
 #pragma unroll
@@ -215,10 +187,10 @@ __global__ __launch_bounds__(VT) void k_pair_kp(ElemArgs a, PairArgs c) {
             s_h[2 * LB + q[k4]] = h[3 * k4 + 2];
         }
     __syncthreads();
-    if (has) reduce_slot<T>(a, s_h, LB, gv0, hp0, j00, j10);
+    if (has) reduce_slot<double>(a, s_h, LB, gv0, hp0, j00, j10);
     for (uint32_t i = tid + VT; i < S; i += VT) {
         const int32_t gvs = bverts[i];
-        if (gvs >= 0) reduce_slot<T>(a, s_h, LB, (uint32_t)gvs, bhpos[i], brow[i], brow[i + 1]);
+        if (gvs >= 0) reduce_slot<double>(a, s_h, LB, (uint32_t)gvs, bhpos[i], brow[i], brow[i + 1]);
     }
     pk = block_sum(pk, s12);
     if (tid == 0) c.part_k[blk] = pk;
@@ -346,23 +318,17 @@ __global__ __launch_bounds__(VT) void k_pair_check(PairArgs c) {
     if (threadIdx.x == 0) pair_record(c, rz, rr, rz / rz0, conv);
 }
 
-template <class T, int MODEL, int W>
+template <int MODEL, int W>
 void launch_kp(const ElemArgs &a, const PairArgs &c, bool first, unsigned grid, size_t shmem, hipStream_t s) {
-    if (first) hipLaunchKernelGGL((k_pair_kp<T, MODEL, W, true>), dim3(grid), dim3(VT), shmem, s, a, c);
-    else hipLaunchKernelGGL((k_pair_kp<T, MODEL, W, false>), dim3(grid), dim3(VT), shmem, s, a, c);
+    if (first) hipLaunchKernelGGL((k_pair_kp<MODEL, W, true>), dim3(grid), dim3(VT), shmem, s, a, c);
+    else hipLaunchKernelGGL((k_pair_kp<MODEL, W, false>), dim3(grid), dim3(VT), shmem, s, a, c);
 }
 
 template <int MODEL>
 void launch_kp(const ebbx_fem_s *F, const ElemArgs &a, const PairArgs &c, bool first, unsigned grid, size_t shmem,
                hipStream_t s) {
-    if (F->prec == EBBX_F32) {
-        if (F->blk_w == 1) launch_kp<float, MODEL, 1>(a, c, first, grid, shmem, s);
-        else if (F->blk_w == 3) launch_kp<float, MODEL, 3>(a, c, first, grid, shmem, s);
-        else launch_kp<float, MODEL, 2>(a, c, first, grid, shmem, s);
-    } else {
-        if (F->blk_w == 1) launch_kp<double, MODEL, 1>(a, c, first, grid, shmem, s);
-        else launch_kp<double, MODEL, 2>(a, c, first, grid, shmem, s);
-    }
+    if (F->blk_w == 1) launch_kp<MODEL, 1>(a, c, first, grid, shmem, s);
+    else launch_kp<MODEL, 2>(a, c, first, grid, shmem, s);
 }
 
 }  // namespace
@@ -370,7 +336,7 @@ void launch_kp(const ebbx_fem_s *F, const ElemArgs &a, const PairArgs &c, bool f
 bool pair_ok(const ebbx_fem_s *F) {
     return F->nm == 1 && F->strategy == EBBX_STRAT_BLOCK && F->blk_red == 0 && F->blk_tpt == 1 &&
            F->blk_tets == VT && F->halo_level == 0 && F->nt > 0 &&
-           F->nblk <= (F->prec == EBBX_F32 ? PAIR_BLOCKS_F32 : PAIR_BLOCKS);
+           F->nblk <= PAIR_BLOCKS && F->prec == EBBX_F64;
 }
 
 void pair_prepare(ebbx_fem_s *F, hipStream_t s) {
