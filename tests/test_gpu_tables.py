@@ -102,3 +102,22 @@ def test_tables_in_a_locality_order(model, prec):
         check(ref)
         fem.set_strategy(ebbx.STRAT_BLOCK, 512 | ebbx.BLOCK_TPT2)
         check(ref)
+
+
+@pytest.mark.parametrize("n,bt,morton", [(13, 64, False), (13, 64, True), (13, 256, True), (20, 64, False)])
+def test_halo_rows(n, bt, morton):
+    """Halo rows of one width (lattice order in blocks of 64 tets: a third of the shared vertices lie in
+    more than 4 blocks) and of two, through the maps and a step.  Normwise 1e-10, FP64."""
+    m = mg.jitter(mg.kuhn_cube(n), 0.01, seed=0)
+    mesh = ebbx.FemMesh(m.X, m.tets, m.pinned, model=1, elem_prec=ebbx.F64, E=1e5, nu=0.3,
+                        strategy=ebbx.STRAT_BLOCK, block=bt, morton=morton)
+    ref = oracle.FEM.create(1, m.X, m.tets, 1e5, 0.3, pinned=m.pinned)
+    d, u = mg.perturbed_state(m, 0.02, seed=10), mg.direction(m, 11)
+    dd, du = mesh.to_dev(d), mesh.to_dev(u)
+    err = lambda got, want: np.abs(mesh.from_dev(got) - want).max() / np.abs(want).max()
+    assert err(mesh.fem.forces(dd), ref.forces(d)) <= 1e-10
+    assert err(mesh.fem.kmul(dd, du), ref.kmul(d, u)) <= 1e-10
+    x, v = mesh.to_dev(d), mesh.to_dev(0.01 * u)
+    mesh.fem.implicit_step(x, v, 1e-3, tol=0.0, maxit=12)
+    _d1, v1, _dv, _s = ref.implicit_step(d, 0.01 * u, 1e-3, tol=0.0, maxit=12)
+    assert err(v, v1) <= 1e-10
