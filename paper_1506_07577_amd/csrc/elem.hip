@@ -726,7 +726,7 @@ __device__ __forceinline__ void halo_row(const double *halo, const int4 *tab, ui
 }
 
 // The same sum with each shared vertex's halo positions in one fixed-width row: one dependent load
-// fewer.  The first n4 rows hold at most 4 positions (92% of them at 64^3 cells), the others up to
+// fewer.  The first n4 rows hold at most 4 positions (89% of them at 64^3 cells), the others up to
 // 4 NC; workgroups [0, g4) take the former.  With rows of 4 NC for every vertex the pass read
 // padding for a third of its bytes and met up to 12 conditional loads in a row: force + K u at 64^3
 // (FP32) 63.9 us with those, 63.3 with rows of two widths, 61.0 with each int4's entries loaded
