@@ -483,7 +483,9 @@ static MortonFrame morton_frame(const double *X, int64_t nv, hipStream_t s) {
         hipLaunchKernelGGL(k_bbox, dim3(nb), dim3(256), 0, s, X, nv, part.as<double>());
         HIPCHK(hipGetLastError());
         std::vector<double> h((size_t)nb * 6);
-        HIPCHK(hipMemcpy(h.data(), part.get(), h.size() * sizeof(double), hipMemcpyDeviceToHost));
+        // on s, after k_bbox: a copy on the null stream does not wait for a non-blocking s
+        HIPCHK(hipMemcpyAsync(h.data(), part.get(), h.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
         double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
         for (unsigned b = 0; b < nb; ++b)
             for (int a = 0; a < 3; ++a) {
