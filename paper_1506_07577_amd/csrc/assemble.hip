@@ -341,14 +341,14 @@ __global__ __launch_bounds__(AB_THREADS) void k_asm_block(AsmBlockArgs a) {
                 for (int i = 0; i < 3; ++i)
 #pragma unroll
                     for (int k = 0; k < 3; ++k) {
-                        // rounded to the element precision, summed in FP64
-                        double v = sizeof(T) == 8 ? acc[3 * i + k] : 0.0;
+                        // the tet's block entry, formed before it joins the sum (the sum is rounded
+                        // once per tet); rounded to the element precision, summed in FP64
+                        double v = 0.0;
                         if (i == k) v += sab;
                         if (MODEL == EBBX_STVK) v += mab * r[R::FF + sym3(i, k)];
                         v += u[i] * x[k];
                         v += w[i] * y[k];
-                        if (sizeof(T) == 8) acc[3 * i + k] = v;
-                        else acc[3 * i + k] += (double)(T)v;
+                        acc[3 * i + k] += (double)(T)v;
                     }
             }
 #pragma unroll
@@ -371,12 +371,11 @@ __global__ __launch_bounds__(AB_THREADS) void k_asm_block(AsmBlockArgs a) {
             for (int32_t j = j0 - g0; j < j1 - g0; ++j) {
                 const uint32_t c = s_ent[j], ca = c & 3u;
                 const double *r = s_rec + R::N * (c >> 4);
-                double v = sizeof(T) == 8 ? acc : 0.0;
+                double v = 0.0;
                 if (i == l) v += r[R::S + ca];
                 if (MODEL == EBBX_STVK) v += r[R::M + ca] * r[f];
                 v += (r[R::P] + r[R::Q]) * r[3 * ca + i] * r[3 * ca + l];
-                if (sizeof(T) == 8) acc = v;
-                else acc += (double)(T)v;
+                acc += (double)(T)v;
             }
             out[(size_t)(3 * i + l) * a.ne + e] = (T)acc;
             if (i != l) out[(size_t)(3 * l + i) * a.ne + e] = (T)acc;
