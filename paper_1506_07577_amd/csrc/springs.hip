@@ -105,8 +105,8 @@ __global__ void k_spring_setup(const int64_t *rp, const int32_t *inc, const int3
     }
 }
 
-// len / sqrt(n2), 0 for n2 = 0 (a zero-length spring pulls with K dq), where n2 is 0 or in
-// [1e-280, 1e280].  One hardware reciprocal square root (about 2^-24) serves the root and the
+// len / sqrt(n2), 0 for n2 = 0 (a zero-length spring pulls with K dq), where len is finite and n2 is 0
+// or in [1e-280, 1e280].  One hardware reciprocal square root (about 2^-24) serves the root and the
 // quotient: two coupled Newton steps give the root and half its reciprocal, a residual step
 // corrects the root, another the quotient.  No branch, so that the loads of the edges after it can
 // be issued before it.  Bit for bit the library's len / sqrt(n2) on 4M random arguments each in
@@ -296,11 +296,13 @@ __device__ __forceinline__ bool spring_list(const int32_t *row, const int32_t *h
     return true;
 }
 
-// got[0]: the most vertices that a workgroup stages (2^30 if one has too many edges); off[4 wg + w]:
+// got[0]: the most vertices that a workgroup stages (2^30 if one has too many edges, or a rest length
+// that is not finite, for which spring_scale's quotient is not the library's); off[4 wg + w]:
 // entries of wave w (its longest vertex's rounds, 64 entries each); *staged: all lists together.
 template <int L>
-__global__ __launch_bounds__(SB_T) void k_spring_count(const int32_t *row, const int32_t *head, int64_t nv, int *most,
-                                                       unsigned long long *staged, int64_t *off) {
+__global__ __launch_bounds__(SB_T) void k_spring_count(const int32_t *row, const int32_t *head, const double *rest,
+                                                       int64_t nv, int *most, unsigned long long *staged,
+                                                       int64_t *off) {
     __shared__ uint32_t s[SB_MAX];
     __shared__ int32_t s_n[SB_T], s_deg[4];
     constexpr int V = SB_T / L, W = 64 / L;   // vertices per workgroup and per wave
@@ -308,6 +310,9 @@ __global__ __launch_bounds__(SB_T) void k_spring_count(const int32_t *row, const
     if (threadIdx.x < 4) s_deg[threadIdx.x] = 0;
     int32_t nu = 0;
     const bool fits = spring_list(row, head, v0, v1, s, s_n, &nu);   // uniform over the workgroup
+    bool finite = true;
+    for (int32_t e = row[v0] + (int32_t)threadIdx.x; e < row[v1]; e += SB_T) finite = finite && isfinite(rest[e]);
+    if (!finite) atomicMax(most, 1 << 30);
     __syncthreads();
     const int64_t v = v0 + threadIdx.x;
     if (threadIdx.x < V && v < v1) atomicMax(&s_deg[threadIdx.x / W], row[v + 1] - row[v]);
@@ -474,7 +479,7 @@ SpringBlocks spring_blocks(const ebbx_springs_s *S) {
 // The tables of k_spring_block, where they pay: the workgroups' lists together hold at most half as
 // many vertices as there are edges (else staging saves little), each few enough for six workgroups'
 // LDS per CU, and padding the waves to their longest vertex adds at most half (else a few vertices
-// of high degree make every lane of their wave wait).  Synchronous.
+// of high degree make every lane of their wave wait), and every rest length is finite.  Synchronous.
 template <int L> void build_spring_blocks(ebbx_springs_s *S, hipStream_t s) {
     const int64_t nv = S->nv, ne = S->ne;
     if (nv == 0 || ne == 0) return;
@@ -484,8 +489,8 @@ template <int L> void build_spring_blocks(ebbx_springs_s *S, hipStream_t s) {
     HIPCHK(hipMemsetAsync(got.get(), 0, 16, s));
     HIPCHK(hipMemsetAsync(S->b_off.get(), 0, S->b_off.bytes(), s));
     hipLaunchKernelGGL(k_spring_count<L>, dim3((unsigned)nwg), dim3(SB_T), 0, s, S->row.as<int32_t>(),
-                       S->head.as<int32_t>(), nv, got.as<int>(), got.as<unsigned long long>() + 1,
-                       S->b_off.as<int64_t>());
+                       S->head.as<int32_t>(), S->rest.as<double>(), nv, got.as<int>(),
+                       got.as<unsigned long long>() + 1, S->b_off.as<int64_t>());
     HIPCHK(hipGetLastError());
     exclusive_scan_i64(S->b_off.as<int64_t>(), 4 * nwg + 1, s);
     int64_t h[2] = {0, 0}, entries = 0;
