@@ -238,6 +238,7 @@ constexpr int SB_STRIDE = 1024;            // staged vertices of one workgroup (
 
 struct SpringBlocks {
     const int32_t *list, *own;   // [nwg * stride], [nwg]
+    const int32_t *row;          // vertex v's edges are [row[v], row[v + 1])
     const int64_t *off;          // [4 nwg + 1]: first entry of each wave, 64 per edge round
     const uint16_t *slot;        // head's place in the workgroup's list
     const double *rest;
@@ -439,7 +440,9 @@ __global__ __launch_bounds__(SB_T) void k_spring_block(SpringBlocks t, double K,
     }
     if (!fine) {   // a spring of extreme or no finite length: this lane's sum again
         a0 = a1 = a2 = 0.0;
-        for (int32_t r = 0; r < rounds; ++r) {
+        // its own edges alone: from a place that is not finite, a padding entry is no zero force
+        const int32_t deg = in ? t.row[v + 1] - t.row[v] : 0, own = (deg - (int32_t)(tid % L) + L - 1) / L;
+        for (int32_t r = 0; r < own; ++r) {
             const uint32_t k = t.slot[j0 + (int64_t)r * 64];
             const double x = s_q[k] - q0, y = s_q[S + k] - q1, z = s_q[2 * S + k] - q2;
             const double sc = spring_scale_any(t.rest[j0 + (int64_t)r * 64], x * x + y * y + z * z);
@@ -472,8 +475,9 @@ __global__ __launch_bounds__(SB_T) void k_spring_block(SpringBlocks t, double K,
 }
 
 SpringBlocks spring_blocks(const ebbx_springs_s *S) {
-    return SpringBlocks{S->b_list.as<int32_t>(), S->b_own.as<int32_t>(), S->b_off.as<int64_t>(),
-                        S->b_slot.as<uint16_t>(), S->b_rest.as<double>(), (uint32_t)S->stride, (uint32_t)S->nv};
+    return SpringBlocks{S->b_list.as<int32_t>(), S->b_own.as<int32_t>(), S->row.as<int32_t>(),
+                        S->b_off.as<int64_t>(), S->b_slot.as<uint16_t>(), S->b_rest.as<double>(),
+                        (uint32_t)S->stride, (uint32_t)S->nv};
 }
 
 // The tables of k_spring_block, where they pay: the workgroups' lists together hold at most half as

@@ -1,8 +1,8 @@
-"""The staged spring kernels (k_spring_block) where a rest length is not finite, and the accuracy of
-their square root and quotient.
+"""The staged spring kernels (k_spring_block) where a length or a position is not finite, and the
+accuracy of their square root and quotient.
 
 A spring of infinite rest length pulls without bound along its direction, as the quotient of the
-library's division does."""
+library's division does; a vertex that no edge leaves has no force wherever it is."""
 import math
 from fractions import Fraction
 
@@ -47,6 +47,28 @@ def test_infinite_rest_length():
     assert np.isinf(want).any()
     sm = ebbx.SpringMesh(X, tail, head, 0.5)
     _same(sm.from_dev(sm.springs.forces(sm.to_dev(q))), want)
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("nv", [321, 70001])   # four and two lanes per vertex
+def test_vertex_without_edges_at_no_finite_position(nv, value):
+    X, tail, head = _ring(nv)
+    lone = 200
+    keep = (tail != lone) & (head != lone)
+    tail, head = tail[keep], head[keep]
+    q = X + 0.01 * np.random.default_rng(2).uniform(-1, 1, X.shape)
+    q[lone] = value
+    want = oracle.Springs(X, tail, head, np.ones(nv), 0.5).forces(q)
+    assert not want[lone].any() and np.isfinite(want).all()
+    sm = ebbx.SpringMesh(X, tail, head, 0.5)
+    got = sm.from_dev(sm.springs.forces(sm.to_dev(q)))
+    assert not got[lone].any()
+    _same(got, want)
+    # one step leaves its velocity as it is
+    v0 = np.random.default_rng(3).uniform(-1, 1, X.shape)
+    a, b = sm.to_dev(q), sm.to_dev(v0)
+    sm.springs.run(sm.scalar_to_dev(np.ones(nv)), 1e-4, 2, a, b, torch.zeros_like(a))
+    assert np.array_equal(sm.from_dev(b)[lone], v0[lone])
 
 
 def _root(n2, bits=80):
