@@ -15,6 +15,7 @@ struct PairArgs {
     int maxit, nch, par;     // par: parity of this iteration, the r.z slot it writes
     int record;              // 1: this iteration's k_pair_kp records the end of the one before
     uint32_t wg0;            // first workgroup of the vertex chunks
+    const uint8_t *pinned;
 };
 
 // Tet blocks of a mesh up to which an iteration runs in two kernels: 44^3 cells have 1997, where
