@@ -150,9 +150,9 @@ def use_torch_allocator(on: bool = True):
     """Route the library's hidden-field allocations through torch's caching allocator."""
     L = lib()
     if on:
-        a, f = _ALLOC_T(_torch_alloc), _FREE_T(_torch_free)
-        _hooks[:] = [a, f]
-        _check(L.ebbx_set_allocator(a, f, None))
+        if not _hooks:   # made once: live objects release their memory through them
+            _hooks[:] = [_ALLOC_T(_torch_alloc), _FREE_T(_torch_free)]
+        _check(L.ebbx_set_allocator(*_hooks, None))
     else:
         _check(L.ebbx_set_allocator(_ALLOC_T(), _FREE_T(), None))
 
