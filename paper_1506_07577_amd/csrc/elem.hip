@@ -993,6 +993,16 @@ static void launch_halo(ebbx_fem_s *F, const double *hl, double *out, int accumu
     HIPCHK(hipGetLastError());
 }
 
+// A strategy set while memory was short can leave the tables of the one before freed.
+static void check_tables(const ebbx_fem_s *F) {
+    bool whole = true;
+    if (F->strategy == EBBX_STRAT_OWNER) whole = F->own_vb > 0;
+    else if (F->strategy == EBBX_STRAT_PIPE) whole = F->halo_level > 0;
+    else if (F->strategy == EBBX_STRAT_BLOCK || F->strategy == EBBX_STRAT_BLOCK_LDS || F->strategy == EBBX_STRAT_LANES)
+        whole = F->blocks_built && F->halo_level == 0;
+    if (!whole) fail(EBBX_E_STATE, "the strategy's tables are not whole (an earlier change of strategy failed); set it again");
+}
+
 void elem_launch(ebbx_fem_s *F, ElemOp op, const double *d, const double *u, double *out, int accumulate,
                  hipStream_t s, const int *skip, const double *w, const int *mdone, bool finish_halo,
                  void *scratch, const int32_t *act) {
@@ -1002,6 +1012,7 @@ void elem_launch(ebbx_fem_s *F, ElemOp op, const double *d, const double *u, dou
         if (!accumulate) fill_f64(out, 3 * nv, 0.0, s);
         return;
     }
+    check_tables(F);
     ElemArgs a = base_args(F);
     set_vec(a.d, d, (uint32_t)nv);
     set_vec(a.u, u, (uint32_t)nv);
@@ -1281,6 +1292,7 @@ __global__ void k_material(const double *E_tet, const double *nu_tet, double E, 
 void elem_set_material(ebbx_fem_s *F, const double *E_tet, const double *nu_tet, double E, double nu, hipStream_t s) {
     const int64_t nt = std::max<int64_t>(F->nt, 1);
     if (!F->mat.get()) F->mat.reset((size_t)nt * 2 * F->esize, s);
+    if (F->ordered && !F->mat_ord.get()) F->mat_ord.reset((size_t)nt * 2 * F->esize, s);   // may fail: before any change
     F->per_tet = true;
     F->E_tet = E_tet;
     F->E = E;
@@ -1393,6 +1405,7 @@ HaloView elem_halo_view(const ebbx_fem_s *F) {
 }
 
 ElemArgs elem_block_args(ebbx_fem_s *F, ElemOp op, const double *d, const double *u, double *out, size_t *shmem) {
+    check_tables(F);
     ElemArgs a = base_args(F);
     set_vec(a.d, d, (uint32_t)F->nv);
     set_vec(a.u, u, (uint32_t)F->nv);
@@ -1715,7 +1728,7 @@ void build_owner(ebbx_fem_s *F, int32_t vb, hipStream_t s) {
         tptr[(size_t)b + 1] = (int32_t)(meta.size() / 4);
         gptr[(size_t)b + 1] = (int32_t)ghost.size();
     }
-    F->own_vb = vb;
+    F->own_vb = 0;   // until the tables below are whole
     F->own_nblk = nblk;
     F->own_maxv = maxv;
     F->own_maxinc = maxinc;
@@ -1728,6 +1741,7 @@ void build_owner(ebbx_fem_s *F, int32_t vb, hipStream_t s) {
     up(F->own_meta, meta.data(), meta.size() * sizeof(uint32_t));
     up(F->own_gptr, gptr.data(), gptr.size() * sizeof(int32_t));
     up(F->own_ghost, ghost.data(), ghost.size() * sizeof(int32_t));
+    F->own_vb = vb;
 }
 
 }  // namespace ebbx

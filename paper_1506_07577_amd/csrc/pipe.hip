@@ -304,6 +304,8 @@ void build_pipe(ebbx_fem_s *F, int32_t g, hipStream_t s) {
     std::vector<int32_t> hpos;
     F->pair_tab.release();
     F->act_mesh.release();
+    F->blocks_built = false;   // the block tables are the PIPE ones now (no block-level halo)
+    F->halo_level = -1;        // until the tables below are whole
     F->ordered = false;   // over the rows' own order
     build_halo(F, sv_all, own_all, rp, hpos, s);
     upload_block_tables(F, hb, {}, s);
@@ -322,7 +324,6 @@ void build_pipe(ebbx_fem_s *F, int32_t g, hipStream_t s) {
     F->sb_maxv = maxsv;
     F->stage_stride = hb.maxv <= 128 ? 128 : 256;
     F->halo_level = g;
-    F->blocks_built = false;   // the block tables are the PIPE ones now (no block-level halo)
 }
 
 }  // namespace ebbx
