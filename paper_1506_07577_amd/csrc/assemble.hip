@@ -14,8 +14,8 @@
 //    corner blocks of the tets holding both of its vertices in ascending tet
 //    order (deterministic).  No per-tet matrix goes through memory;
 //  - k_elem_matrix and k_edge_gather: the same blocks through a 144-value record
-//    per tet in memory, for meshes with a vertex of so many tets (over 400
-//    neo-Hookean or 240 StVK) that their records do not fit in LDS;
+//    per tet in memory, for meshes with a vertex of so many tets (some 400
+//    neo-Hookean or 240 StVK) that those of four vertices do not fit in LDS;
 //  - k_bsr_spmv: sixteen lanes per vertex row; each lane takes edges of the row
 //    (consecutive lanes read consecutive entries of each column) and the row
 //    sum is a fixed butterfly over the sixteen lanes.
@@ -171,6 +171,12 @@ constexpr int AB_OFF = 128;
 constexpr int TB_THREADS = 256;         // table construction
 constexpr int AB_MAXINC = 4096;          // incidences of one workgroup's vertices (table construction)
 constexpr size_t AB_LDS = 80 * 1024;     // most LDS of one workgroup: two workgroups per CU
+// Fewest vertices of a workgroup: every workgroup reserves the LDS of the fullest, so one vertex of many
+// tets takes the whole mesh to fewer vertices in fewer workgroups per CU, and few vertices share few
+// evaluations.  384k tets and one such vertex, at two workgroups per CU, against the path through memory:
+// 8 vertices 142 against 402 us, 4 214 to 220 against 373 to 402 (FP32 elements 282 to 313), 2 368 to 370
+// against 373 to 402 (282 to 313), 1 698 to 708 against 373 to 418.
+constexpr int32_t AB_MINVB = 4;
 
 // LDS of a workgroup with at most `tets` records and the entries of `inc` incidences (4 each)
 size_t asm_lds(int32_t model, int64_t tets, int64_t inc) {
@@ -581,7 +587,7 @@ __global__ __launch_bounds__(TB_THREADS) void k_asm_fill(const int64_t *rp, cons
 // The edges relation and the entry lists from the grouping's keys: the 16 nt corner blocks sorted
 // by (tail, head), stably, so that an edge's entries ascend in (tet, corner, corner); then the
 // workgroups' tables of k_asm_block: 8 vertices per workgroup (neo-Hookean) or 4 (StVK), measured
-// at the kernel, or as many fewer as the LDS takes.  Once per domain, synchronous.
+// at the kernel, or 4 where the LDS does not take 8.  Once per domain, synchronous.
 void build_edges(ebbx_fem_s *F, hipStream_t s) {
     if (F->n_edges >= 0) return;
     const int64_t nt = F->nt, nv = F->nv, n = 16 * nt;
@@ -622,7 +628,7 @@ void build_edges(ebbx_fem_s *F, hipStream_t s) {
     F->a_vb = 0;
     const int64_t *rp = F->group->row_ptr.as<int64_t>();
     const int32_t *inc = F->group->inc.as<int32_t>();
-    for (int32_t vb = F->model == EBBX_NH ? 8 : 4; vb >= 1 && ne > 0 && n < (int64_t(1) << 31) && !F->a_vb; vb /= 2) {
+    for (int32_t vb = F->model == EBBX_NH ? 8 : 4; vb >= AB_MINVB && ne > 0 && n < (int64_t(1) << 31) && !F->a_vb; vb /= 2) {
         const int64_t nwg = (nv + vb - 1) / vb;
         DevBuf base(room(nwg + 1, 8), s), mx(16, s);
         HIPCHK(hipMemsetAsync(mx.get(), 0, 2 * sizeof(int), s));
