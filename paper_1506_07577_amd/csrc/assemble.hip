@@ -22,6 +22,7 @@
 #include <algorithm>
 
 #include "fem.h"
+#include "sort.h"
 #include "tetmath.h"
 #include "wave.h"
 
@@ -479,50 +480,14 @@ __global__ void k_edge_rows(const uint64_t *key, const int64_t *at, int64_t n, i
 // The distinct tets of vertices [v0, v1), sorted ascending into s[0, *nu); false if they have
 // more than AB_MAXINC incidences.
 __device__ __forceinline__ bool tets_of(const int64_t *rp, const int32_t *inc, int64_t v0, int64_t v1, uint32_t *s,
-                                        int32_t *s_n, int32_t *nu) {
+                                        int32_t *sw, int32_t *nu) {
     const int64_t p0 = rp[v0], ninc = rp[v1] - p0;
     if (ninc > AB_MAXINC) return false;
     int32_t n = 64;
     while (n < ninc) n <<= 1;
     for (int32_t i = threadIdx.x; i < n; i += TB_THREADS) s[i] = i < ninc ? (uint32_t)inc[p0 + i] >> 2 : ~0u;
-    __syncthreads();
-    for (int32_t k = 2; k <= n; k <<= 1)
-        for (int32_t j = k >> 1; j > 0; j >>= 1) {
-            for (int32_t e = threadIdx.x; e < n / 2; e += TB_THREADS) {
-                const int32_t i = ((e & ~(j - 1)) << 1) | (e & (j - 1)), o = i | j;
-                const uint32_t x = s[i], y = s[o];
-                if ((x > y) == ((i & k) == 0)) {
-                    s[i] = y;
-                    s[o] = x;
-                }
-            }
-            __syncthreads();
-        }
-    // compact in place: every thread reads its stretch before any writes
-    const int32_t per = (n + TB_THREADS - 1) / TB_THREADS, i0 = (int32_t)threadIdx.x * per;
-    uint32_t keep[AB_MAXINC / TB_THREADS];
-    int32_t m = 0;
-#pragma unroll
-    for (int32_t u = 0; u < AB_MAXINC / TB_THREADS; ++u) {
-        const int32_t i = i0 + u;
-        keep[u] = ~0u;
-        if (u < per && i < n && s[i] != ~0u && (i == 0 || s[i] != s[i - 1])) {
-            keep[u] = s[i];
-            ++m;
-        }
-    }
-    s_n[threadIdx.x] = m;
-    __syncthreads();
-    int32_t at = 0, total = 0;
-    for (int32_t w = 0; w < TB_THREADS; ++w) {
-        if (w < (int32_t)threadIdx.x) at += s_n[w];
-        total += s_n[w];
-    }
-#pragma unroll
-    for (int32_t u = 0; u < AB_MAXINC / TB_THREADS; ++u)
-        if (keep[u] != ~0u) s[at++] = keep[u];
-    __syncthreads();
-    *nu = total;
+    lds_sort<TB_THREADS>(s, n);
+    *nu = lds_distinct<TB_THREADS, AB_MAXINC>(s, n, sw);
     return true;
 }
 
@@ -530,10 +495,10 @@ __device__ __forceinline__ bool tets_of(const int64_t *rp, const int32_t *inc, i
 __global__ __launch_bounds__(TB_THREADS) void k_asm_count(const int64_t *rp, const int32_t *inc, int64_t nv, int32_t vb,
                                                           int64_t *count, int *most) {
     __shared__ uint32_t s[AB_MAXINC];
-    __shared__ int32_t s_n[TB_THREADS];
+    __shared__ int32_t sw[TB_THREADS / 64];
     const int64_t v0 = (int64_t)blockIdx.x * vb, v1 = v0 + vb < nv ? v0 + vb : nv;
     int32_t nu = 0;
-    const bool fits = tets_of(rp, inc, v0, v1, s, s_n, &nu);   // uniform over the workgroup
+    const bool fits = tets_of(rp, inc, v0, v1, s, sw, &nu);   // uniform over the workgroup
     if (threadIdx.x == 0) {
         count[blockIdx.x] = fits ? nu : 0;
         atomicMax(most, fits ? nu : 1 << 30);
@@ -548,10 +513,10 @@ __global__ __launch_bounds__(TB_THREADS) void k_asm_fill(const int64_t *rp, cons
                                                          int32_t *tptr, int32_t *tets, int4 *tkeys, int32_t *diag,
                                                          uint16_t *ent) {
     __shared__ uint32_t s[AB_MAXINC];
-    __shared__ int32_t s_n[TB_THREADS];
+    __shared__ int32_t sw[TB_THREADS / 64];
     const int64_t v0 = (int64_t)blockIdx.x * vb, v1 = v0 + vb < nv ? v0 + vb : nv;
     int32_t nu = 0;
-    if (!tets_of(rp, inc, v0, v1, s, s_n, &nu)) return;
+    if (!tets_of(rp, inc, v0, v1, s, sw, &nu)) return;
     const int64_t t0 = base[blockIdx.x];
     if (threadIdx.x == 0) {
         tptr[blockIdx.x] = (int32_t)t0;

@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "fem.h"
+#include "sort.h"
 #include "wave.h"
 
 struct ebbx_springs_s {
@@ -248,7 +249,7 @@ struct SpringBlocks {
 // The distinct vertices that workgroup wg's vertices and edges touch, sorted into s[0, *nu); false
 // if there are more than SB_MAX of them with repeats.
 __device__ __forceinline__ bool spring_list(const int32_t *row, const int32_t *head, int64_t v0, int64_t v1,
-                                            uint32_t *s, int32_t *s_n, int32_t *nu) {
+                                            uint32_t *s, int32_t *sw, int32_t *nu) {
     const int64_t e0 = row[v0], ne = row[v1] - e0, own = v1 - v0;
     if (ne + own > SB_MAX) return false;
     const int32_t m = (int32_t)(ne + own);
@@ -256,44 +257,8 @@ __device__ __forceinline__ bool spring_list(const int32_t *row, const int32_t *h
     while (n < m) n <<= 1;
     for (int32_t i = threadIdx.x; i < n; i += SB_T)
         s[i] = i < ne ? (uint32_t)head[e0 + i] : i < m ? (uint32_t)(v0 + i - ne) : ~0u;
-    __syncthreads();
-    for (int32_t k = 2; k <= n; k <<= 1)
-        for (int32_t j = k >> 1; j > 0; j >>= 1) {
-            for (int32_t e = threadIdx.x; e < n / 2; e += SB_T) {
-                const int32_t i = ((e & ~(j - 1)) << 1) | (e & (j - 1)), o = i | j;
-                const uint32_t x = s[i], y = s[o];
-                if ((x > y) == ((i & k) == 0)) {
-                    s[i] = y;
-                    s[o] = x;
-                }
-            }
-            __syncthreads();
-        }
-    // compact in place: every thread reads its stretch before any writes
-    const int32_t per = n / SB_T, i0 = (int32_t)threadIdx.x * per;
-    uint32_t keep[SB_MAX / SB_T];
-    int32_t cnt = 0;
-#pragma unroll
-    for (int32_t u = 0; u < SB_MAX / SB_T; ++u) {
-        const int32_t i = i0 + u;
-        keep[u] = ~0u;
-        if (u < per && s[i] != ~0u && (i == 0 || s[i] != s[i - 1])) {
-            keep[u] = s[i];
-            ++cnt;
-        }
-    }
-    s_n[threadIdx.x] = cnt;
-    __syncthreads();
-    int32_t at = 0, total = 0;
-    for (int32_t w = 0; w < SB_T; ++w) {
-        if (w < (int32_t)threadIdx.x) at += s_n[w];
-        total += s_n[w];
-    }
-#pragma unroll
-    for (int32_t u = 0; u < SB_MAX / SB_T; ++u)
-        if (keep[u] != ~0u) s[at++] = keep[u];
-    __syncthreads();
-    *nu = total;
+    lds_sort<SB_T>(s, n);
+    *nu = lds_distinct<SB_T, SB_MAX>(s, n, sw);
     return true;
 }
 
@@ -305,12 +270,12 @@ __global__ __launch_bounds__(SB_T) void k_spring_count(const int32_t *row, const
                                                        int64_t nv, int *most, unsigned long long *staged,
                                                        int64_t *off) {
     __shared__ uint32_t s[SB_MAX];
-    __shared__ int32_t s_n[SB_T], s_deg[4];
+    __shared__ int32_t sw[SB_T / 64], s_deg[4];
     constexpr int V = SB_T / L, W = 64 / L;   // vertices per workgroup and per wave
     const int64_t v0 = (int64_t)blockIdx.x * V, v1 = v0 + V < nv ? v0 + V : nv;
     if (threadIdx.x < 4) s_deg[threadIdx.x] = 0;
     int32_t nu = 0;
-    const bool fits = spring_list(row, head, v0, v1, s, s_n, &nu);   // uniform over the workgroup
+    const bool fits = spring_list(row, head, v0, v1, s, sw, &nu);   // uniform over the workgroup
     bool finite = true;
     for (int32_t e = row[v0] + (int32_t)threadIdx.x; e < row[v1]; e += SB_T) finite = finite && isfinite(rest[e]);
     if (!finite) atomicMax(most, 1 << 30);
@@ -331,11 +296,11 @@ __global__ __launch_bounds__(SB_T) void k_spring_fill(const int32_t *row, const 
                                                       int64_t nv, int32_t stride, const int64_t *off, int32_t *list,
                                                       int32_t *own, uint16_t *slot, double *brest) {
     __shared__ uint32_t s[SB_MAX];
-    __shared__ int32_t s_n[SB_T];
+    __shared__ int32_t sw[SB_T / 64];
     constexpr int V = SB_T / L;
     const int64_t wg = blockIdx.x, v0 = wg * V, v1 = v0 + V < nv ? v0 + V : nv;
     int32_t nu = 0;
-    if (!spring_list(row, head, v0, v1, s, s_n, &nu)) return;
+    if (!spring_list(row, head, v0, v1, s, sw, &nu)) return;
     auto place = [&](uint32_t v) {
         int32_t lo = 0, hi = nu - 1;
         while (lo < hi) {

@@ -18,6 +18,7 @@
 #include <algorithm>
 
 #include "fem.h"
+#include "sort.h"
 
 namespace ebbx {
 
@@ -39,41 +40,7 @@ __device__ __forceinline__ void sorted_pairs(const int32_t *keys, int64_t nt, in
         const int32_t i = c < 4 ? 4 * tl + c : e;
         s[i] = in ? ((unsigned long long)(uint32_t)keys[(int64_t)c * nt + t0 + tl] << 12) | (unsigned)i : ~0ull;
     }
-    __syncthreads();
-    for (int32_t k = 2; k <= n; k <<= 1)
-        for (int32_t j = k >> 1; j > 0; j >>= 1) {
-            for (int32_t e = tid; e < n / 2; e += BT_THREADS) {
-                const int32_t i = ((e & ~(j - 1)) << 1) | (e & (j - 1)), o = i | j;
-                const unsigned long long x = s[i], y = s[o];
-                if ((x > y) == ((i & k) == 0)) {
-                    s[i] = y;
-                    s[o] = x;
-                }
-            }
-            __syncthreads();
-        }
-}
-
-// Exclusive prefix of x over the workgroup's threads and the total (sw: one entry per wave).
-__device__ __forceinline__ int32_t block_prefix(int32_t x, int32_t *sw, int32_t &total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int32_t v = x;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int32_t y = __shfl_up(v, o, 64);
-        if (lane >= o) v += y;
-    }
-    __syncthreads();
-    if (lane == 63) sw[wave] = v;
-    __syncthreads();
-    int32_t off = 0;
-    total = 0;
-#pragma unroll
-    for (int w = 0; w < BT_THREADS / 64; ++w) {
-        if (w < wave) off += sw[w];
-        total += sw[w];
-    }
-    return off + v - x;
+    lds_sort<BT_THREADS>(s, n);
 }
 
 // Thread tid's stretch of the sorted pairs, [tid * n / 256, ...): head h of a vertex's run, with
@@ -107,8 +74,8 @@ __global__ __launch_bounds__(BT_THREADS) void k_blk_count(const int32_t *keys, c
         shared += sh;
     });
     int32_t nb = 0, ns = 0;
-    block_prefix(heads, sw, nb);
-    block_prefix(shared, sw, ns);
+    block_prefix<BT_THREADS>(heads, sw, nb);
+    block_prefix<BT_THREADS>(shared, sw, ns);
     if (threadIdx.x == 0) {
         nsh[b] = ns;
         atomicMax(maxv, nb);
@@ -141,8 +108,8 @@ __global__ __launch_bounds__(BT_THREADS) void k_blk_fill(const unsigned long lon
         shared += sh;
     });
     int32_t nb = 0, ns = 0;
-    int32_t slot = block_prefix(heads, sw, nb);
-    int64_t hp = hbase[b] + block_prefix(shared, sw, ns);
+    int32_t slot = block_prefix<BT_THREADS>(heads, sw, nb);
+    int64_t hp = hbase[b] + block_prefix<BT_THREADS>(shared, sw, ns);
     const int64_t left = nt - b * bt;
     const int32_t ntl = left < bt ? (int32_t)left : bt;   // tets of this block
     each_head(s_pairs, n, rp, [&](int32_t i, uint32_t v, int32_t len, bool sh) {
