@@ -491,9 +491,9 @@ __device__ __forceinline__ bool tets_of(const int64_t *rp, const int32_t *inc, i
     return true;
 }
 
-// Tets per workgroup of vb vertices into count[wg], the most tets and incidences of any into most[].
+// Tets per workgroup of vb vertices into count[wg], the most tets and incidences of any into most[0], most[1].
 __global__ __launch_bounds__(TB_THREADS) void k_asm_count(const int64_t *rp, const int32_t *inc, int64_t nv, int32_t vb,
-                                                          int64_t *count, int *most) {
+                                                          int64_t *count, Tally *most) {
     __shared__ uint32_t s[AB_MAXINC];
     __shared__ int32_t sw[TB_THREADS / 64];
     const int64_t v0 = (int64_t)blockIdx.x * vb, v1 = v0 + vb < nv ? v0 + vb : nv;
@@ -501,8 +501,8 @@ __global__ __launch_bounds__(TB_THREADS) void k_asm_count(const int64_t *rp, con
     const bool fits = tets_of(rp, inc, v0, v1, s, sw, &nu);   // uniform over the workgroup
     if (threadIdx.x == 0) {
         count[blockIdx.x] = fits ? nu : 0;
-        atomicMax(most, fits ? nu : 1 << 30);
-        atomicMax(most + 1, fits ? (int)(rp[v1] - rp[v0]) : 0);
+        most[0].add(fits ? nu : 1 << 30, 0);
+        most[1].add(fits ? rp[v1] - rp[v0] : 0, 0);
     }
 }
 
@@ -595,18 +595,19 @@ void build_edges(ebbx_fem_s *F, hipStream_t s) {
     const int32_t *inc = F->group->inc.as<int32_t>();
     for (int32_t vb = F->model == EBBX_NH ? 8 : 4; vb >= AB_MINVB && ne > 0 && n < (int64_t(1) << 31) && !F->a_vb; vb /= 2) {
         const int64_t nwg = (nv + vb - 1) / vb;
-        DevBuf base(room(nwg + 1, 8), s), mx(16, s);
-        HIPCHK(hipMemsetAsync(mx.get(), 0, 2 * sizeof(int), s));
+        DevBuf base(room(nwg + 1, 8), s), mx(2 * sizeof(Tally), s);
+        HIPCHK(hipMemsetAsync(mx.get(), 0, mx.bytes(), s));
         HIPCHK(hipMemsetAsync(base.get(), 0, base.bytes(), s));
         hipLaunchKernelGGL(k_asm_count, dim3((unsigned)nwg), dim3(TB_THREADS), 0, s, rp, inc, nv, vb,
-                           base.as<int64_t>(), mx.as<int>());
+                           base.as<int64_t>(), mx.as<Tally>());
         HIPCHK(hipGetLastError());
         exclusive_scan_i64(base.as<int64_t>(), nwg + 1, s);
-        int most[2] = {0, 0};
+        Tally found[2] = {};
         int64_t total = 0;
-        HIPCHK(hipMemcpyAsync(most, mx.get(), sizeof most, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipMemcpyAsync(found, mx.get(), sizeof found, hipMemcpyDeviceToHost, s));
         HIPCHK(hipMemcpyAsync(&total, base.as<int64_t>() + nwg, sizeof total, hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
+        const int64_t most[2] = {found[0].largest(), found[1].largest()};
         if (asm_lds(F->model, most[0], most[1]) > AB_LDS || total >= (int64_t(1) << 31)) continue;
         F->a_tptr.reset(room(nwg + 1, 4), s);
         F->a_tets.reset(room(total, 4), s);
@@ -621,8 +622,8 @@ void build_edges(ebbx_fem_s *F, hipStream_t s) {
         HIPCHK(hipGetLastError());
         HIPCHK(hipStreamSynchronize(s));
         F->e_gent.release();
-        F->a_most = most[0];
-        F->a_inc = most[1];
+        F->a_most = (int32_t)most[0];
+        F->a_inc = (int32_t)most[1];
         F->a_vb = vb;
     }
     HIPCHK(hipStreamSynchronize(s));

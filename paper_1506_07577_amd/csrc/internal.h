@@ -152,6 +152,8 @@ std::shared_ptr<Grouping> build_group(ebbx_relation_s *rel, const char *name, hi
 
 // Device primitives of the runtime (runtime.hip).
 void exclusive_scan_i64(int64_t *data, int64_t n, hipStream_t s);  // in place, n entries
+int64_t scan_scratch(int64_t n);   // tile totals over all levels of a scan of n entries
+void exclusive_scan_i64(int64_t *data, int64_t n, int64_t *scratch, hipStream_t s);   // scan_scratch(n) entries; no wait
 // Stable LSD radix sort of (key, value) pairs on the low `bits` bits of key.
 void radix_sort_pairs_u32(uint32_t *keys, uint32_t *vals, int64_t n, int bits, hipStream_t s);
 void radix_sort_pairs_u64(uint64_t *keys, uint32_t *vals, int64_t n, int bits, hipStream_t s);

@@ -177,8 +177,7 @@ __global__ void k_scan_add(int64_t *data, int64_t n, const int64_t *offs) {
     }
 }
 
-// Tile totals over all levels of a scan of n entries.
-static int64_t scan_scratch(int64_t n) {
+int64_t scan_scratch(int64_t n) {
     int64_t total = 0;
     do {
         n = (n + SCAN_TILE - 1) / SCAN_TILE;
@@ -197,6 +196,10 @@ static void scan_levels(int64_t *data, int64_t n, int64_t *sums, hipStream_t s) 
         hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(SCAN_T), 0, s, data, n, sums);
         HIPCHK(hipGetLastError());
     }
+}
+
+void exclusive_scan_i64(int64_t *data, int64_t n, int64_t *scratch, hipStream_t s) {
+    if (n > 0) scan_levels(data, n, scratch, s);
 }
 
 void exclusive_scan_i64(int64_t *data, int64_t n, hipStream_t s) {

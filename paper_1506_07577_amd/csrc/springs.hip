@@ -247,62 +247,111 @@ struct SpringBlocks {
 };
 
 // The distinct vertices that workgroup wg's vertices and edges touch, sorted into s[0, *nu); false
-// if there are more than SB_MAX of them with repeats.
+// if there are more than SB_MAX of them with repeats.  The heads beyond the workgroup's own [v0, v1)
+// pass through a hash table first (a vertex is the head of some 4 edges of a workgroup), so that only
+// distinct ones are sorted, and the own ones go into their place among them.  With all of them sorted
+// k_spring_count took 94 us in place of 59 at 64^3 cells.
 __device__ __forceinline__ bool spring_list(const int32_t *row, const int32_t *head, int64_t v0, int64_t v1,
                                             uint32_t *s, int32_t *sw, int32_t *nu) {
-    const int64_t e0 = row[v0], ne = row[v1] - e0, own = v1 - v0;
+    const int64_t e0 = row[v0], ne = row[v1] - e0;
+    const int32_t own = (int32_t)(v1 - v0);
     if (ne + own > SB_MAX) return false;
-    const int32_t m = (int32_t)(ne + own);
-    int32_t n = 256;
-    while (n < m) n <<= 1;
-    for (int32_t i = threadIdx.x; i < n; i += SB_T)
-        s[i] = i < ne ? (uint32_t)head[e0 + i] : i < m ? (uint32_t)(v0 + i - ne) : ~0u;
+    int32_t n = 64;
+    while (n < ne) n <<= 1;   // a place for every head: the probing ends
+    for (int32_t i = threadIdx.x; i < n; i += SB_T) s[i] = ~0u;
+    __syncthreads();
+    for (int32_t i0 = 0; i0 < ne; i0 += 4 * SB_T) {
+        int32_t h[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int32_t i = i0 + u * SB_T + (int32_t)threadIdx.x;
+            h[u] = i < ne ? head[e0 + i] : (int32_t)v0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (h[u] >= v0 && h[u] < v1) continue;
+            uint32_t at = ((uint32_t)h[u] * 2654435761u >> 16) & (uint32_t)(n - 1), was;
+            while ((was = atomicCAS(s + at, ~0u, (uint32_t)h[u])) != ~0u && was != (uint32_t)h[u])
+                at = (at + 1) & (uint32_t)(n - 1);
+        }
+    }
+    __syncthreads();
+    const int32_t k = lds_distinct<SB_T, SB_MAX>(s, n, sw);   // the places taken
+    n = 64;
+    while (n < k) n <<= 1;
+    for (int32_t i = k + (int32_t)threadIdx.x; i < n; i += SB_T) s[i] = ~0u;
     lds_sort<SB_T>(s, n);
-    *nu = lds_distinct<SB_T, SB_MAX>(s, n, sw);
+    int32_t lo = 0, hi = k;   // those below v0
+    while (lo < hi) {
+        const int32_t mid = (lo + hi) >> 1;
+        if ((int64_t)s[mid] < v0) lo = mid + 1;
+        else hi = mid;
+    }
+    uint32_t up[SB_MAX / SB_T];   // the others move up; every thread reads its own before any writes
+#pragma unroll
+    for (int32_t u = 0; u < SB_MAX / SB_T; ++u) {
+        const int32_t i = lo + u * SB_T + (int32_t)threadIdx.x;
+        up[u] = i < k ? s[i] : ~0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int32_t u = 0; u < SB_MAX / SB_T; ++u)
+        if (up[u] != ~0u) s[lo + own + u * SB_T + (int32_t)threadIdx.x] = up[u];
+    for (int32_t i = threadIdx.x; i < own; i += SB_T) s[lo + i] = (uint32_t)(v0 + i);
+    __syncthreads();
+    *nu = k + own;
     return true;
 }
 
-// got[0]: the most vertices that a workgroup stages (2^30 if one has too many edges, or a rest length
-// that is not finite, for which spring_scale's quotient is not the library's); off[4 wg + w]:
-// entries of wave w (its longest vertex's rounds, 64 entries each); *staged: all lists together.
+// A workgroup's staged vertices into *verts (2^30 if there are too many, or with a rest length that is
+// not finite, for which spring_scale's quotient is not the library's); off[4 wg + w]: entries of wave w
+// (its longest vertex's rounds, 64 entries each), all of them into *entries; its list, -1 padded, at
+// list[SB_STRIDE wg].
 template <int L>
 __global__ __launch_bounds__(SB_T) void k_spring_count(const int32_t *row, const int32_t *head, const double *rest,
-                                                       int64_t nv, int *most, unsigned long long *staged,
-                                                       int64_t *off) {
+                                                       int64_t nv, Tally *verts, Tally *entries, int64_t *off,
+                                                       int32_t *list) {
     __shared__ uint32_t s[SB_MAX];
     __shared__ int32_t sw[SB_T / 64], s_deg[4];
     constexpr int V = SB_T / L, W = 64 / L;   // vertices per workgroup and per wave
     const int64_t v0 = (int64_t)blockIdx.x * V, v1 = v0 + V < nv ? v0 + V : nv;
     if (threadIdx.x < 4) s_deg[threadIdx.x] = 0;
     int32_t nu = 0;
-    const bool fits = spring_list(row, head, v0, v1, s, sw, &nu);   // uniform over the workgroup
+    bool fits = spring_list(row, head, v0, v1, s, sw, &nu);   // uniform over the workgroup
     bool finite = true;
-    for (int32_t e = row[v0] + (int32_t)threadIdx.x; e < row[v1]; e += SB_T) finite = finite && isfinite(rest[e]);
-    if (!finite) atomicMax(most, 1 << 30);
-    __syncthreads();
+    for (int32_t e = row[v0] + (int32_t)threadIdx.x, e1 = row[v1]; e < e1; e += SB_T) finite &= isfinite(rest[e]);
+    fits = __syncthreads_and(finite) && fits && nu <= SB_STRIDE;
     const int64_t v = v0 + threadIdx.x;
     if (threadIdx.x < V && v < v1) atomicMax(&s_deg[threadIdx.x / W], row[v + 1] - row[v]);
     __syncthreads();
-    if (threadIdx.x < 4)
-        off[4 * (int64_t)blockIdx.x + threadIdx.x] = fits ? (int64_t)((s_deg[threadIdx.x] + L - 1) / L) * 64 : 0;
+    auto places = [&](int w) { return fits ? (int64_t)((s_deg[w] + L - 1) / L) * 64 : 0; };
+    if (threadIdx.x < 4) off[4 * (int64_t)blockIdx.x + threadIdx.x] = places(threadIdx.x);
     if (threadIdx.x == 0) {
-        atomicMax(most, fits ? nu : 1 << 30);
-        atomicAdd(staged, (unsigned long long)nu);
+        if (blockIdx.x + 1 == gridDim.x) off[4 * (int64_t)gridDim.x] = 0;   // scanned with the others
+        verts->add(fits ? nu : 1 << 30, fits ? (unsigned long long)nu : 0);
+        entries->add(0, (unsigned long long)(places(0) + places(1) + places(2) + places(3)));
     }
+    if (fits)
+        for (int32_t i = threadIdx.x; i < SB_STRIDE; i += SB_T)
+            list[SB_STRIDE * (int64_t)blockIdx.x + i] = i < nu ? (int32_t)s[i] : -1;
 }
 
 template <int L>
 __global__ __launch_bounds__(SB_T) void k_spring_fill(const int32_t *row, const int32_t *head, const double *rest,
-                                                      int64_t nv, int32_t stride, const int64_t *off, int32_t *list,
-                                                      int32_t *own, uint16_t *slot, double *brest) {
-    __shared__ uint32_t s[SB_MAX];
-    __shared__ int32_t sw[SB_T / 64];
+                                                      int64_t nv, int32_t stride, const int64_t *off,
+                                                      const int32_t *from, int32_t *list, int32_t *own,
+                                                      uint16_t *slot, double *brest) {
+    __shared__ uint32_t s[SB_STRIDE];   // the padding sorts last
     constexpr int V = SB_T / L;
-    const int64_t wg = blockIdx.x, v0 = wg * V, v1 = v0 + V < nv ? v0 + V : nv;
-    int32_t nu = 0;
-    if (!spring_list(row, head, v0, v1, s, sw, &nu)) return;
+    const int64_t wg = blockIdx.x, v0 = wg * V;
+    for (int32_t i = threadIdx.x; i < stride; i += SB_T) {
+        const int32_t v = from[SB_STRIDE * wg + i];
+        s[i] = (uint32_t)v;
+        list[wg * stride + i] = v;
+    }
+    __syncthreads();
     auto place = [&](uint32_t v) {
-        int32_t lo = 0, hi = nu - 1;
+        int32_t lo = 0, hi = stride - 1;
         while (lo < hi) {
             const int32_t mid = (lo + hi) >> 1;
             if (s[mid] < v) lo = mid + 1;
@@ -310,7 +359,6 @@ __global__ __launch_bounds__(SB_T) void k_spring_fill(const int32_t *row, const 
         }
         return lo;
     };
-    for (int32_t i = threadIdx.x; i < stride; i += SB_T) list[wg * stride + i] = i < nu ? (int32_t)s[i] : -1;
     const int32_t first = place((uint32_t)v0);
     if (threadIdx.x == 0) own[wg] = first;
     const int32_t lv = (int32_t)threadIdx.x / L, sub = (int32_t)threadIdx.x % L;
@@ -453,21 +501,24 @@ template <int L> void build_spring_blocks(ebbx_springs_s *S, hipStream_t s) {
     const int64_t nv = S->nv, ne = S->ne;
     if (nv == 0 || ne == 0) return;
     const int64_t nwg = (nv + SB_T / L - 1) / (SB_T / L);
-    DevBuf got(16, s);
-    S->b_off.reset((size_t)(4 * nwg + 1) * sizeof(int64_t), s);
-    HIPCHK(hipMemsetAsync(got.get(), 0, 16, s));
-    HIPCHK(hipMemsetAsync(S->b_off.get(), 0, S->b_off.bytes(), s));
+    // the lists of the counting pass; behind them its two tallies and the scratch of the scan
+    const int64_t nlist = nwg * SB_STRIDE, noff = 4 * nwg + 1;
+    DevBuf tmp((size_t)nlist * sizeof(int32_t) + 2 * sizeof(Tally) + (size_t)scan_scratch(noff) * sizeof(int64_t), s);
+    Tally *tally = (Tally *)(tmp.as<int32_t>() + nlist);
+    S->b_off.reset((size_t)noff * sizeof(int64_t), s);
+    HIPCHK(hipMemsetAsync(tally, 0, 2 * sizeof(Tally), s));
     hipLaunchKernelGGL(k_spring_count<L>, dim3((unsigned)nwg), dim3(SB_T), 0, s, S->row.as<int32_t>(),
-                       S->head.as<int32_t>(), S->rest.as<double>(), nv, got.as<int>(),
-                       got.as<unsigned long long>() + 1, S->b_off.as<int64_t>());
+                       S->head.as<int32_t>(), S->rest.as<double>(), nv, tally, tally + 1, S->b_off.as<int64_t>(),
+                       tmp.as<int32_t>());
     HIPCHK(hipGetLastError());
-    exclusive_scan_i64(S->b_off.as<int64_t>(), 4 * nwg + 1, s);
-    int64_t h[2] = {0, 0}, entries = 0;
-    HIPCHK(hipMemcpyAsync(h, got.get(), sizeof h, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(&entries, S->b_off.as<int64_t>() + 4 * nwg, sizeof entries, hipMemcpyDeviceToHost, s));
+    exclusive_scan_i64(S->b_off.as<int64_t>(), noff, (int64_t *)(tally + 2), s);
+    HIPCHK(hipStreamCreateWithFlags(&S->cap, hipStreamNonBlocking));   // while the device counts
+    Tally got[2] = {};
+    HIPCHK(hipMemcpyAsync(got, tally, sizeof got, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    const int32_t most = (int32_t)(h[0] & 0x7fffffff);
-    if (most > SB_STRIDE || 2 * h[1] > ne || 2 * entries > 3 * ne) {
+    const int32_t most = (int32_t)got[0].largest();
+    const int64_t staged = (int64_t)got[0].total(), entries = (int64_t)got[1].total();
+    if (most > SB_STRIDE || 2 * staged > ne || 2 * entries > 3 * ne) {
         S->b_off.release();
         return;
     }
@@ -477,7 +528,7 @@ template <int L> void build_spring_blocks(ebbx_springs_s *S, hipStream_t s) {
     S->b_rest.reset((size_t)entries * sizeof(double), s);
     hipLaunchKernelGGL(k_spring_fill<L>, dim3((unsigned)nwg), dim3(SB_T), 0, s, S->row.as<int32_t>(),
                        S->head.as<int32_t>(), S->rest.as<double>(), nv, most, S->b_off.as<int64_t>(),
-                       S->b_list.as<int32_t>(), S->b_own.as<int32_t>(), S->b_slot.as<uint16_t>(),
+                       tmp.as<int32_t>(), S->b_list.as<int32_t>(), S->b_own.as<int32_t>(), S->b_slot.as<uint16_t>(),
                        S->b_rest.as<double>());
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(s));
@@ -629,7 +680,7 @@ extern "C" ebbx_status ebbx_springs_create(ebbx_relation edges, const char *tail
     HIPCHK(hipGetLastError());
     if (S->nv <= SB_FOUR_NV) build_spring_blocks<4>(S.get(), nullptr);
     else build_spring_blocks<2>(S.get(), nullptr);
-    HIPCHK(hipStreamCreateWithFlags(&S->cap, hipStreamNonBlocking));
+    if (!S->cap) HIPCHK(hipStreamCreateWithFlags(&S->cap, hipStreamNonBlocking));
     HIPCHK(hipDeviceSynchronize());
     {
         std::lock_guard<std::mutex> lk(g_mu);

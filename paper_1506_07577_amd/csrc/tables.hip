@@ -58,11 +58,10 @@ __device__ __forceinline__ void each_head(const unsigned long long *s, int32_t n
     }
 }
 
-// Pass 1: the block's shared vertices into nsh[b], the largest vertex count of a block into *maxv,
-// all blocks' vertices together into *staged.
+// Pass 1: the block's shared vertices into nsh[b], its vertex count into *verts.
 __global__ __launch_bounds__(BT_THREADS) void k_blk_count(const int32_t *keys, const int64_t *rp, int64_t nt,
                                                           int32_t bt, int32_t n, unsigned long long *pairs,
-                                                          int64_t *nsh, int *maxv, unsigned long long *staged) {
+                                                          int64_t *nsh, Tally *verts) {
     extern __shared__ unsigned long long s_pairs[];
     __shared__ int32_t sw[BT_THREADS / 64];
     const int64_t b = blockIdx.x;
@@ -78,8 +77,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_blk_count(const int32_t *keys, c
     block_prefix<BT_THREADS>(shared, sw, ns);
     if (threadIdx.x == 0) {
         nsh[b] = ns;
-        atomicMax(maxv, nb);
-        atomicAdd(staged, (unsigned long long)nb);
+        verts->add(nb, (unsigned long long)nb);
     }
 }
 
@@ -244,22 +242,21 @@ Counted count_blocks(const int32_t *keys, const int64_t *rp, int64_t nt, int32_t
     const int32_t n = pairs_of(bt);
     c.hbase.reset((size_t)(nblk + 1) * sizeof(int64_t), s);
     c.pairs.reset(std::max<size_t>((size_t)nblk * 4 * bt * sizeof(unsigned long long), 16), s);
-    DevBuf mx(16, s);
-    HIPCHK(hipMemsetAsync(mx.get(), 0, 16, s));
+    DevBuf verts(sizeof(Tally), s);
+    HIPCHK(hipMemsetAsync(verts.get(), 0, sizeof(Tally), s));
     HIPCHK(hipMemsetAsync(c.hbase.get(), 0, c.hbase.bytes(), s));
     if (nblk > 0) {
         hipLaunchKernelGGL(k_blk_count, dim3((unsigned)nblk), dim3(BT_THREADS), (size_t)n * 8, s, keys, rp, nt, bt, n,
-                           c.pairs.as<unsigned long long>(), c.hbase.as<int64_t>(), mx.as<int>(),
-                           mx.as<unsigned long long>() + 1);
+                           c.pairs.as<unsigned long long>(), c.hbase.as<int64_t>(), verts.as<Tally>());
         HIPCHK(hipGetLastError());
     }
     exclusive_scan_i64(c.hbase.as<int64_t>(), nblk + 1, s);
-    int64_t got[2] = {0, 0};
-    HIPCHK(hipMemcpyAsync(got, mx.get(), sizeof got, hipMemcpyDeviceToHost, s));
+    Tally got{};
+    HIPCHK(hipMemcpyAsync(&got, verts.get(), sizeof got, hipMemcpyDeviceToHost, s));
     HIPCHK(hipMemcpyAsync(&c.halo, c.hbase.as<int64_t>() + nblk, sizeof c.halo, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    c.maxv = std::max((int32_t)(got[0] & 0x7fffffff), 1);
-    c.staged = got[1];
+    c.maxv = std::max((int32_t)got.largest(), 1);
+    c.staged = (int64_t)got.total();
     return c;
 }
 
