@@ -13,7 +13,7 @@ namespace ebbx {
 // another.  Atomics on one address pass one by one, some 10 ns each (of 69k workgroups' two, 1.3 of the
 // 1.6 ms that a count took), so both are spread over places, and only a larger value is sent.
 struct Tally {
-    static constexpr int PLACES = 64;
+    static constexpr int PLACES = 16;
     long long most[PLACES];
     unsigned long long sum[PLACES];
     // by one thread of a workgroup
