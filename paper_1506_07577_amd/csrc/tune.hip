@@ -5,9 +5,9 @@
 // per-element matrix work is register-heavy (Discussion).  Here the choice
 // between scatter strategies, their block sizes and tets per thread is made
 // by timing the stiffness product, the call a CG iteration spends most of its
-// time in, on the domain itself.  Choices are cached in a small JSON file keyed by the
-// device, the element model and precision, the sizes and a fingerprint of
-// the tets' keys (locality decides between strategies).
+// time in, on the domain itself.  Choices are cached in a small JSON file keyed by a
+// revision of what is timed, the device, the element model and precision, the sizes and a
+// fingerprint of the tets' keys (locality decides between strategies).
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -48,7 +48,14 @@ uint64_t fnv1a(const void *p, size_t n, uint64_t h) {
     return h;
 }
 
-// device | model | precision | material | sizes | fingerprint of up to 64Ki sampled keys
+// What the candidates' ranking rests on besides the domain: raised when kernels or tables change it, so
+// that a choice made by an earlier build is timed again.  2: the BLOCK tables of rows without locality
+// follow an order of their own (force + K u of 635k scrambled tets 272 -> 55 us), which SEG, PIPE and
+// LANES do not.
+constexpr int kTuneRevision = 2;
+
+// revision | device | model | precision | material | sizes | whether the tables may follow an order of
+// their own | fingerprint of up to 64Ki sampled keys
 std::string cache_key(ebbx_fem_s *F, hipStream_t s) {
     int dev = 0;
     HIPCHK(hipGetDevice(&dev));
@@ -66,9 +73,9 @@ std::string cache_key(ebbx_fem_s *F, hipStream_t s) {
     }
     const uint64_t h = fnv1a(sample.data(), sample.size() * sizeof(int32_t), 1469598103934665603ull);
     char buf[256];
-    std::snprintf(buf, sizeof buf, "%s/%dcu|m%d|p%d|e%d|nt%lld|nv%lld|nm%lld|k%016llx", prop.gcnArchName,
-                  prop.multiProcessorCount, F->model, F->prec, F->per_tet ? 1 : 0, (long long)F->nt, (long long)F->nv,
-                  (long long)F->nm, (unsigned long long)h);
+    std::snprintf(buf, sizeof buf, "r%d|%s/%dcu|m%d|p%d|e%d|nt%lld|nv%lld|nm%lld|o%d|k%016llx", kTuneRevision,
+                  prop.gcnArchName, prop.multiProcessorCount, F->model, F->prec, F->per_tet ? 1 : 0, (long long)F->nt,
+                  (long long)F->nv, (long long)F->nm, F->may_order ? 1 : 0, (unsigned long long)h);
     for (char *c = buf; *c; ++c)
         if (*c == '"' || *c == '\\') *c = '_';
     return buf;
