@@ -1614,14 +1614,13 @@ void build_halo(ebbx_fem_s *F, const std::vector<int32_t> &verts, const std::vec
     F->halo.reset((size_t)std::max<int64_t>(F->halo_n, 1) * 3 * sizeof(double), s);
 }
 
-// Upload the block tables (without the halo): fixed-stride copies, block b's
-// vertices at [b*maxv, (b+1)*maxv) padded with -1 (halo positions hpos alike) and
-// its block-relative row starts at [b*(maxv+1), (b+1)*(maxv+1)); per tet the corner
-// rows and the packed slots.
-void upload_block_tables(ebbx_fem_s *F, const HostBlocks &hb, const std::vector<int32_t> &hpos, hipStream_t s) {
+// Upload the block tables (without the halo, which is of the super-blocks): fixed-stride copies,
+// block b's vertices at [b*maxv, (b+1)*maxv) padded with -1 and its block-relative row starts at
+// [b*(maxv+1), (b+1)*(maxv+1)); per tet the corner rows and the packed slots.
+void upload_block_tables(ebbx_fem_s *F, const HostBlocks &hb, hipStream_t s) {
     const int64_t nblk = hb.nblk;
     const size_t S = (size_t)hb.maxv;
-    std::vector<int32_t> pverts((size_t)nblk * S, -1), phpos((size_t)nblk * S, -1);
+    std::vector<int32_t> pverts((size_t)nblk * S, -1);
     std::vector<uint16_t> prow((size_t)nblk * (S + 1), 0);
     for (int64_t b = 0; b < nblk; ++b) {
         const int32_t a0 = hb.vptr[(size_t)b], a1 = hb.vptr[(size_t)b + 1];
@@ -1630,7 +1629,6 @@ void upload_block_tables(ebbx_fem_s *F, const HostBlocks &hb, const std::vector<
             const int32_t k = a0 + (int32_t)i;
             if (k < a1) {
                 pverts[(size_t)b * S + i] = hb.verts[(size_t)k];
-                if (!hpos.empty()) phpos[(size_t)b * S + i] = hpos[(size_t)k];
                 prow[(size_t)b * (S + 1) + i] = (uint16_t)(hb.lptr[(size_t)k] - base);
             } else {
                 prow[(size_t)b * (S + 1) + i] = (uint16_t)tot;
@@ -1640,8 +1638,8 @@ void upload_block_tables(ebbx_fem_s *F, const HostBlocks &hb, const std::vector<
     upload(F->blk_verts, pverts.data(), pverts.size() * sizeof(int32_t), s);
     upload(F->blk_lptr, prow.data(), prow.size() * sizeof(uint16_t), s);
     upload(F->blk_pos, hb.pos.data(), hb.pos.size() * sizeof(uint32_t), s);
-    upload(F->blk_hpos, phpos.data(), phpos.size() * sizeof(int32_t), s);
     upload(F->blk_local, hb.packed.data(), hb.packed.size() * sizeof(uint32_t), s);
+    F->blk_hpos.release();
     F->blk_tets = hb.bt;
     F->nblk = nblk;
     F->blk_maxv = hb.maxv;

@@ -212,7 +212,7 @@ void upload(DevBuf &dst, const void *src, size_t bytes, hipStream_t s);
 // lists, in unit order, are verts (own: the unit holds every incident tet).
 void build_halo(ebbx_fem_s *F, const std::vector<int32_t> &verts, const std::vector<uint8_t> &own,
                 const std::vector<int64_t> &rp, std::vector<int32_t> &hpos, hipStream_t s);
-void upload_block_tables(ebbx_fem_s *F, const HostBlocks &hb, const std::vector<int32_t> &hpos, hipStream_t s);
+void upload_block_tables(ebbx_fem_s *F, const HostBlocks &hb, hipStream_t s);
 // Build the tet-block tables of the BLOCK strategies with a halo of the blocks' shared vertices,
 // on the device (tables.hip).  reorder: the tables may follow a locality order of the tets
 // (t_order) where the rows' own order has none.

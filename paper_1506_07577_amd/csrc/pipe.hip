@@ -308,7 +308,7 @@ void build_pipe(ebbx_fem_s *F, int32_t g, hipStream_t s) {
     F->halo_level = -1;        // until the tables below are whole
     F->ordered = false;   // over the rows' own order
     build_halo(F, sv_all, own_all, rp, hpos, s);
-    upload_block_tables(F, hb, {}, s);
+    upload_block_tables(F, hb, s);
     const size_t SV = (size_t)maxsv;
     std::vector<int32_t> pverts((size_t)nsb * SV, -1), phpos((size_t)nsb * SV, -1);
     for (int64_t q = 0; q < nsb; ++q)
