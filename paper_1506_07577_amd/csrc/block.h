@@ -7,10 +7,11 @@
 
 namespace ebbx {
 
-// Block b holds tets [b*BT, (b+1)*BT), BT = blockDim.x * TPT.  Its vertex list
-// blk_verts[vptr[b] .. vptr[b+1]) is sorted; each corner carries its slot in
-// that list (packed: 4 x 8 bits per word when every block has <= 256 vertices,
-// else 2 x 16 bits in each of two words).
+// Block b holds tets [b*BT, (b+1)*BT) of the tables' order, BT = blockDim.x * TPT.
+// Its vertex list blk_verts[b*S .. (b+1)*S), S the largest block's count, is sorted
+// and padded with -1; each corner carries its slot in that list (packed: 4 x 8 bits
+// per word when every block has <= 256 vertices, else 2 x 16 bits in each of two
+// words).
 
 template <int W> __device__ __forceinline__ void unpack_slots(const ElemArgs &a, uint32_t t, uint32_t *s) {
     if (W != 2) {

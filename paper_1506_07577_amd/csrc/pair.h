@@ -23,11 +23,11 @@ struct PairArgs {
 constexpr int64_t PAIR_BLOCKS = 2048;
 
 // Whether F's solves run so: one mesh, BLOCK strategy with 256 tets per block, one per thread,
-// incidence-order sums, at most PAIR_BLOCKS blocks, FP64 elements.  With FP32 elements the two would be
-// 1.4x the faster too (up to 27^3 cells), but p.Kp summed over the tets differs from the vertices' sum in
-// the last bit, and where that turns an FP32 rounding of a tet's gradients the solves part: measured
-// by 4e-10 normwise and 1.5e-8 in the largest entry at 16^3 (to 1e-8), 5e-8 at 43^3 (100 iterations),
-// where a solve should not depend on its kernels by more than 1e-9 and 4e-8.
+// incidence-order sums, at most PAIR_BLOCKS blocks, FP64 elements.  Solves with FP32 elements keep the plain
+// iteration, and so their bits: p.Kp summed over the tets differs from the vertices' sum in the last place,
+// and where that turns an FP32 rounding of a tet's gradients two solves part by 4e-10 normwise and 1.5e-8
+// in the largest entry at 16^3 cells (to 1e-8), 5e-8 at 43^3 (100 iterations).  Neither is further from
+// 64-bit arithmetic, and the two kernels would be up to 1.4x the faster (27^3).
 bool pair_ok(const ebbx_fem_s *F);
 // The per-vertex halo places that the iterations read (pair_tab), whole on return; before they are
 // captured.

@@ -108,9 +108,10 @@ __global__ void k_spring_setup(const int64_t *rp, const int32_t *inc, const int3
 
 // len / sqrt(n2), 0 for n2 = 0 (a zero-length spring pulls with K dq), where len is finite and n2 is 0
 // or in [1e-280, 1e280].  One hardware reciprocal square root (about 2^-24) serves the root and the
-// quotient: two coupled Newton steps give the root and half its reciprocal, a residual step
-// corrects the root, another the quotient.  No branch, so that the loads of the edges after it can
-// be issued before it.  Bit for bit the library's len / sqrt(n2) on 4M random arguments each in
+// quotient: two steps of Goldschmidt's coupled iteration (g to the root, h to half its reciprocal;
+// Markstein 1990) and residual corrections of the root and of the quotient.  No branch, so that the
+// loads of the edges after it can be issued before it.  Within one ulp (tested against exact
+// arithmetic); no bit differed from len / sqrt(n2) of the library on 4M random arguments each in
 // [0.5, 1.5] x [0.25, 3.25], over 9 and 17 decades and over 260 and 555 decades.
 __device__ __forceinline__ double spring_scale(double len, double n2) {
     const double y = __builtin_amdgcn_rsq(n2);

@@ -11,7 +11,8 @@
 // (vertices per block fix the tables' stride, shared vertices the halo's places); a
 // second pass writes the tables from the sorted pairs, 32 bytes per tet kept in
 // memory between the two (sorting again instead took 75 us of the second pass's 80,
-// 2,000 blocks).  Bound by the barriers of the sort's stages.  The tables equal those of host_blocks (elem.hip) entry for entry.
+// 2,000 blocks).  k_blk_count takes 141 us for 6,144 blocks of 256 tets (194 with its
+// tallies' atomics on one address); fewer barriers in the sort's 55 stages gained nothing.
 // Measured, a new scrambled mesh of 358k tets taken in (relations, Morton order, domain,
 // mass, one force; FP32): 71.9 ms with the tables built on the host and each pass of the
 // radix sort waited for, 1.60 ms with these.
@@ -365,10 +366,13 @@ void build_blocks(ebbx_fem_s *F, int32_t bt, bool reorder, hipStream_t s) {
     // fixed-width rows of halo places when no vertex has more than 16
     F->sh_n = sh_n;
     F->sh_nc = maxm <= 16 ? std::max(1, (maxm + 3) / 4) : 0;
-    // Rows of two widths where seven eighths have at most 4 places: the vertices of the second width
-    // are written apart from their neighbours' lines.  Two widths against one, force + K u, FP32:
-    // 64^3 cells in Morton order, 89% narrow (other Morton orders up to 93%), 60.3 against 65.1 us;
-    // 90^3 in lattice order, 86% narrow, 168.6 against 163.5.
+    // Rows of two widths where seven eighths have at most 4 places.  They spare the padding of the narrow
+    // rows and part the wide rows' vertices from their neighbours' lines, so the share decides, though not
+    // alone.  Two widths against one, force + K u, 32^3 to 80^3 cells, Morton and lattice order, blocks of 64
+    // to 512 tets, FP32 and FP64 (60 pairs): from seven eighths on 0.98 to 1.07 of the speed with rows of up
+    // to 12 places (1.02 on average: 64^3 in Morton order, 89% narrow, 63.9 -> 61.2 us in FP32) and 0.97 to
+    // 1.03 with up to 8 (1.00 on average: 80^3 in lattice order, 93%, 105.4 -> 107.5 us); below it 0.89 to 1.03, the least at
+    // 80^3 (72%, 111.0 -> 124.6 us).
     if (F->sh_nc == 0 || n4 * 8 < sh_n * 7) n4 = 0;
     F->sh_n4 = n4;
     F->sh_vert.reset(room(sh_n, 4), s);
