@@ -371,8 +371,8 @@ void build_blocks(ebbx_fem_s *F, int32_t bt, bool reorder, hipStream_t s) {
     // alone.  Two widths against one, force + K u, 32^3 to 80^3 cells, Morton and lattice order, blocks of 64
     // to 512 tets, FP32 and FP64 (60 pairs): from seven eighths on 0.98 to 1.07 of the speed with rows of up
     // to 12 places (1.02 on average: 64^3 in Morton order, 89% narrow, 63.9 -> 61.2 us in FP32) and 0.97 to
-    // 1.03 with up to 8 (1.00 on average: 80^3 in lattice order, 93%, 105.4 -> 107.5 us); below it 0.89 to 1.03, the least at
-    // 80^3 (72%, 111.0 -> 124.6 us).
+    // 1.03 with up to 8 (1.00 on average: 80^3 in lattice order, 93%, 105.4 -> 107.5 us); below it 0.89 to
+    // 1.03, the least at 80^3 (72%, 111.0 -> 124.6 us).
     if (F->sh_nc == 0 || n4 * 8 < sh_n * 7) n4 = 0;
     F->sh_n4 = n4;
     F->sh_vert.reset(room(sh_n, 4), s);
