@@ -31,16 +31,17 @@ struct ebbx_springs_s {
     const ebbx_relation_s *edges = nullptr, *verts = nullptr;   // the relations the row copies follow
     int64_t nv = 0, ne = 0;
     double K = 0.0;
-    ebbx::DevBuf row;    // int32 (nv + 1): vertex v's edges are [row[v], row[v+1])
+    ebbx::DevBuf row;    // int32 (nv + 1): vertex v's edges are [row[v], row[v+1]); behind them, per workgroup of
+                         // k_spring_block, the place of its first vertex in its list
     ebbx::DevBuf head;   // int32 (ne): head vertex of each edge, in row order
     ebbx::DevBuf rest;   // FP64 (ne): rest length of each edge, in row order
     ebbx::DevBuf part;   // FP64 partials of the energy sum
     ebbx::DevBuf q2;     // FP64 (3 nv): the other position buffer of the fused steps of a run
     // k_spring_block (stride 0: not used), `lanes` lanes per vertex: per workgroup the sorted list of
-    // the vertices it reads (-1 padded to the stride) and the place of its own first one; per wave
-    // its edges, padded to the same number per lane, lane-major
+    // the vertices it reads (-1 padded to the stride); per wave its edges, padded to the same number
+    // per lane, lane-major
     int32_t stride = 0, lanes = 2;
-    ebbx::DevBuf b_list, b_own, b_off, b_slot, b_rest;
+    ebbx::DevBuf b_list, b_off, b_slot, b_rest;
     // captured steps of ebbx_springs_run
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
@@ -239,8 +240,7 @@ constexpr int SB_MAX = 4096;               // edges and vertices of one workgrou
 constexpr int SB_STRIDE = 1024;            // staged vertices of one workgroup (24 KiB of LDS)
 
 struct SpringBlocks {
-    const int32_t *list, *own;   // [nwg * stride], [nwg]
-    const int32_t *row;          // vertex v's edges are [row[v], row[v + 1])
+    const int32_t *list, *own;   // [nwg * stride], [nwg]; the rows' offsets, nv + 1, stand before own
     const int64_t *off;          // [4 nwg + 1]: first entry of each wave, 64 per edge round
     const uint16_t *slot;        // head's place in the workgroup's list
     const double *rest;
@@ -455,7 +455,8 @@ __global__ __launch_bounds__(SB_T) void k_spring_block(SpringBlocks t, double K,
     if (!fine) {   // a spring of extreme or no finite length: this lane's sum again
         a0 = a1 = a2 = 0.0;
         // its own edges alone: from a place that is not finite, a padding entry is no zero force
-        const int32_t deg = in ? t.row[v + 1] - t.row[v] : 0, own = (deg - (int32_t)(tid % L) + L - 1) / L;
+        const int32_t *row = t.own - (size_t)(nv + 1);
+        const int32_t deg = in ? row[v + 1] - row[v] : 0, own = (deg - (int32_t)(tid % L) + L - 1) / L;
         for (int32_t r = 0; r < own; ++r) {
             const uint32_t k = t.slot[j0 + (int64_t)r * 64];
             const double x = s_q[k] - q0, y = s_q[S + k] - q1, z = s_q[2 * S + k] - q2;
@@ -489,9 +490,8 @@ __global__ __launch_bounds__(SB_T) void k_spring_block(SpringBlocks t, double K,
 }
 
 SpringBlocks spring_blocks(const ebbx_springs_s *S) {
-    return SpringBlocks{S->b_list.as<int32_t>(), S->b_own.as<int32_t>(), S->row.as<int32_t>(),
-                        S->b_off.as<int64_t>(), S->b_slot.as<uint16_t>(), S->b_rest.as<double>(),
-                        (uint32_t)S->stride, (uint32_t)S->nv};
+    return SpringBlocks{S->b_list.as<int32_t>(), S->row.as<int32_t>() + S->nv + 1, S->b_off.as<int64_t>(),
+                        S->b_slot.as<uint16_t>(), S->b_rest.as<double>(), (uint32_t)S->stride, (uint32_t)S->nv};
 }
 
 // The tables of k_spring_block, where they pay: the workgroups' lists together hold at most half as
@@ -524,13 +524,12 @@ template <int L> void build_spring_blocks(ebbx_springs_s *S, hipStream_t s) {
         return;
     }
     S->b_list.reset((size_t)nwg * most * sizeof(int32_t), s);
-    S->b_own.reset((size_t)nwg * sizeof(int32_t), s);
     S->b_slot.reset((size_t)entries * sizeof(uint16_t), s);
     S->b_rest.reset((size_t)entries * sizeof(double), s);
     hipLaunchKernelGGL(k_spring_fill<L>, dim3((unsigned)nwg), dim3(SB_T), 0, s, S->row.as<int32_t>(),
                        S->head.as<int32_t>(), S->rest.as<double>(), nv, most, S->b_off.as<int64_t>(),
-                       tmp.as<int32_t>(), S->b_list.as<int32_t>(), S->b_own.as<int32_t>(), S->b_slot.as<uint16_t>(),
-                       S->b_rest.as<double>());
+                       tmp.as<int32_t>(), S->b_list.as<int32_t>(), S->row.as<int32_t>() + nv + 1,
+                       S->b_slot.as<uint16_t>(), S->b_rest.as<double>());
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(s));
     S->stride = most;
@@ -671,7 +670,7 @@ extern "C" ebbx_status ebbx_springs_create(ebbx_relation edges, const char *tail
     S->K = K;
     if (S->ne >= (int64_t(1) << 31)) fail(EBBX_E_ARG, "too many edges");
     auto g = build_group(er, tail, nullptr);
-    S->row.reset((size_t)(S->nv + 1) * sizeof(int32_t));
+    S->row.reset((size_t)(S->nv + 1 + blocks_of(S->nv, SB_T / 4)) * sizeof(int32_t));
     S->head.reset((size_t)std::max<int64_t>(S->ne, 1) * sizeof(int32_t));
     S->rest.reset((size_t)std::max<int64_t>(S->ne, 1) * sizeof(double));
     S->part.reset((size_t)blocks_of(std::max<int64_t>(S->nv, 1), EN_THREADS) * sizeof(double));
