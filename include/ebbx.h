@@ -243,7 +243,9 @@ ebbx_status ebbx_fem_create(ebbx_relation tets, const char *keyfield, ebbx_relat
                             const ebbx_fem_params *params, ebbx_fem *out);
 ebbx_status ebbx_fem_destroy(ebbx_fem fem);
 
-/* Change the scatter strategy and block size of an existing FEM. */
+/* Change the scatter strategy and block size of an existing FEM.  If it fails for
+ * want of memory the strategy stays as it was; calls whose tables it had already
+ * begun to replace then return EBBX_E_STATE until a strategy is set. */
 ebbx_status ebbx_fem_set_strategy(ebbx_fem fem, int32_t strategy, int32_t block);
 /* Read back the strategy and block size in use (after AUTO resolution). */
 ebbx_status ebbx_fem_get_strategy(ebbx_fem fem, int32_t *strategy, int32_t *block);
