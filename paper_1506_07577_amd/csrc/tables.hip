@@ -59,10 +59,10 @@ __device__ __forceinline__ void each_head(const unsigned long long *s, int32_t n
     }
 }
 
-// Pass 1: the block's shared vertices into nsh[b], its vertex count into *verts.
+// Pass 1: the block's shared vertices into nsh[b] and into found[1], its vertex count into found[0].
 __global__ __launch_bounds__(BT_THREADS) void k_blk_count(const int32_t *keys, const int64_t *rp, int64_t nt,
                                                           int32_t bt, int32_t n, unsigned long long *pairs,
-                                                          int64_t *nsh, Tally *verts) {
+                                                          int64_t *nsh, Tally *found) {
     extern __shared__ unsigned long long s_pairs[];
     __shared__ int32_t sw[BT_THREADS / 64];
     const int64_t b = blockIdx.x;
@@ -78,7 +78,9 @@ __global__ __launch_bounds__(BT_THREADS) void k_blk_count(const int32_t *keys, c
     block_prefix<BT_THREADS>(shared, sw, ns);
     if (threadIdx.x == 0) {
         nsh[b] = ns;
-        verts->add(nb, (unsigned long long)nb);
+        if (b + 1 == gridDim.x) nsh[b + 1] = 0;   // scanned with the others
+        found[0].add(nb, (unsigned long long)nb);
+        found[1].add(0, (unsigned long long)ns);
     }
 }
 
@@ -243,21 +245,21 @@ Counted count_blocks(const int32_t *keys, const int64_t *rp, int64_t nt, int32_t
     const int32_t n = pairs_of(bt);
     c.hbase.reset((size_t)(nblk + 1) * sizeof(int64_t), s);
     c.pairs.reset(std::max<size_t>((size_t)nblk * 4 * bt * sizeof(unsigned long long), 16), s);
-    DevBuf verts(sizeof(Tally), s);
-    HIPCHK(hipMemsetAsync(verts.get(), 0, sizeof(Tally), s));
-    HIPCHK(hipMemsetAsync(c.hbase.get(), 0, c.hbase.bytes(), s));
+    // the two tallies and the scratch of the scan
+    DevBuf found(2 * sizeof(Tally) + (size_t)scan_scratch(nblk + 1) * sizeof(int64_t), s);
+    HIPCHK(hipMemsetAsync(found.get(), 0, 2 * sizeof(Tally), s));
+    Tally got[2] = {};
     if (nblk > 0) {
         hipLaunchKernelGGL(k_blk_count, dim3((unsigned)nblk), dim3(BT_THREADS), (size_t)n * 8, s, keys, rp, nt, bt, n,
-                           c.pairs.as<unsigned long long>(), c.hbase.as<int64_t>(), verts.as<Tally>());
+                           c.pairs.as<unsigned long long>(), c.hbase.as<int64_t>(), found.as<Tally>());
         HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpyAsync(got, found.get(), sizeof got, hipMemcpyDeviceToHost, s));
+        exclusive_scan_i64(c.hbase.as<int64_t>(), nblk + 1, (int64_t *)(found.as<Tally>() + 2), s);
     }
-    exclusive_scan_i64(c.hbase.as<int64_t>(), nblk + 1, s);
-    Tally got{};
-    HIPCHK(hipMemcpyAsync(&got, verts.get(), sizeof got, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(&c.halo, c.hbase.as<int64_t>() + nblk, sizeof c.halo, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    c.maxv = std::max((int32_t)got.largest(), 1);
-    c.staged = (int64_t)got.total();
+    c.maxv = std::max((int32_t)got[0].largest(), 1);
+    c.staged = (int64_t)got[0].total();
+    c.halo = (int64_t)got[1].total();
     return c;
 }
 
