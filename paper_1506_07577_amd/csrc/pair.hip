@@ -192,20 +192,17 @@ __global__ __launch_bounds__(VT) void k_pair_kp(ElemArgs a, PairArgs c) {
         const int32_t gvs = bverts[i];
         if (gvs >= 0) reduce_slot<double>(a, s_h, LB, (uint32_t)gvs, bhpos[i], brow[i], brow[i + 1]);
     }
-    double sum = block_sum(pk, s12);
-    if (!isfinite(sum)) {   // uniform
+    if (!isfinite(pk)) {   // so it is in
         // p is zero on pinned vertices, and their rows are no part of the system: a tet of four has no
         // share, also where its stress is not finite (0 * inf)
-        if (in && !isfinite(pk)) {
-            unpack_slots<W>(a, t, sl);
-            bool pinned = true;
+        unpack_slots<W>(a, t, sl);
+        bool pinned = true;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) pinned = pinned && c.pinned[bverts[sl[k]]];
-            if (pinned) pk = 0.0;
-        }
-        sum = block_sum(pk, s12);
+        for (int k = 0; k < 4; ++k) pinned = pinned && c.pinned[bverts[sl[k]]];
+        if (pinned) pk = 0.0;
     }
-    if (tid == 0) c.part_k[blk] = sum;
+    pk = block_sum(pk, s12);
+    if (tid == 0) c.part_k[blk] = pk;
 }
 
 // The halo places of every vertex, W int4 per vertex in block order: -1 padded; all -1 where a
